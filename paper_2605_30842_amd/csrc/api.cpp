@@ -42,6 +42,33 @@ bool uses_mfma(const comem_decode_attn_plan& p);
 constexpr int kCounterWords = 3;
 constexpr int kErrorWord = 2;  // index after the tickets
 
+// Words between two tickets (log2). Atomics on one 128-byte line take their
+// turns, whichever word they name: with the tickets of 8 heads side by side,
+// the 256 workgroups of a batch-1 call waited 1.2 us for their ticket, with
+// a line each 0.4 us. So every ticket gets a line of its own where all of
+// them then still fit the counter region of the allocation-free call (a plan
+// it took with dense tickets it takes with spread ones too); a plan of more
+// sequences has its tickets closer, down to side by side: its workgroups
+// reach them at different times.
+constexpr int kMaxTicketShift = 5;
+
+size_t ticket_region_bytes(int64_t tickets, int shift) {
+  return align256(((static_cast<size_t>(tickets) << shift) + kCounterWords) * 4);
+}
+
+int choose_ticket_shift(int64_t tickets) {
+  int shift = kMaxTicketShift;
+  while (shift > 0 && ticket_region_bytes(tickets, shift) > comem::kScratchTicketBytes) --shift;
+  return shift;
+}
+
+int64_t num_tickets(const comem_decode_attn_plan& p) {
+  return static_cast<int64_t>(p.cfg.max_batch) * p.cfg.num_kv_heads;
+}
+
+// First of the counter words, in words from the workspace's start.
+int64_t counter_slot(const comem_decode_attn_plan& p) { return num_tickets(p) << p.ticket_shift; }
+
 bool debug_checks(const comem_decode_attn_plan& p) { return (p.cfg.flags & COMEM_FLAG_DEBUG_CHECKS) != 0; }
 
 // With debug checks the error word lives in the workspace, so one is needed.
@@ -243,7 +270,7 @@ void fill_common(const comem_decode_attn_plan& p, comem::AttnParams& a, const vo
   const int64_t e = elem_bytes(p.cfg);
   std::memset(&a, 0, sizeof(a));
   a.max_ctx = static_cast<int32_t>(max_ctx_len);
-  if (debug_checks(p)) a.errors = static_cast<uint32_t*>(workspace) + p.cfg.max_batch * p.cfg.num_kv_heads + kErrorWord;
+  if (debug_checks(p)) a.errors = static_cast<uint32_t*>(workspace) + counter_slot(p) + kErrorWord;
   a.q = static_cast<const char*>(q);
   a.k = static_cast<const char*>(k);
   a.v = static_cast<const char*>(v);
@@ -260,7 +287,8 @@ void fill_common(const comem_decode_attn_plan& p, comem::AttnParams& a, const vo
   // An FP8 cache's K scale multiplies every score; its V scale every output.
   a.scale_log2 = p.cfg.scale * (is_fp8(p.cfg) ? p.cfg.k_scale : 1.f) * 1.4426950408889634f;
   a.out_scale = is_fp8(p.cfg) ? p.cfg.v_scale : 1.f;
-  a.queue_slot = p.cfg.max_batch * p.cfg.num_kv_heads;
+  a.queue_slot = static_cast<int32_t>(counter_slot(p));
+  a.ticket_shift = p.ticket_shift;
   if (splits > 1 || queue) {
     char* ws = static_cast<char*>(workspace);
     const size_t slots = static_cast<size_t>(batch) * static_cast<size_t>(splits) *
@@ -395,7 +423,8 @@ comem_status comem_decode_attn_init(const comem_decode_attn_config* cfg, int dev
   p->device = device;
   p->num_cus = num_cus > 0 ? num_cus : kAssumedCUs;
   // tickets (one per sequence and KV head), then the two work-queue counters
-  p->ticket_bytes = align256((static_cast<size_t>(cfg->max_batch) * cfg->num_kv_heads + kCounterWords) * 4);
+  p->ticket_shift = choose_ticket_shift(num_tickets(*p));
+  p->ticket_bytes = ticket_region_bytes(num_tickets(*p), p->ticket_shift);
   // Largest number of (sequence, split) slots any call within the limits plans
   // (bounded for the matrix-core kernel by its smallest split of 1024 tokens);
   // calls with a smaller workspace get coarser splits.
@@ -440,7 +469,7 @@ comem_status comem_decode_attn_device_errors(const comem_decode_attn_plan* plan,
   *errors_out = 0;
   if (p->device == COMEM_NO_DEVICE) return COMEM_ERR_NO_DEVICE;
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
-  uint32_t* word = static_cast<uint32_t*>(workspace) + p->cfg.max_batch * p->cfg.num_kv_heads + kErrorWord;
+  uint32_t* word = static_cast<uint32_t*>(workspace) + counter_slot(*p) + kErrorWord;
   uint32_t host = 0;
   if (hipMemcpyAsync(&host, word, sizeof(host), hipMemcpyDeviceToHost, s) != hipSuccess) return COMEM_ERR_HIP;
   if (hipStreamSynchronize(s) != hipSuccess) return COMEM_ERR_HIP;

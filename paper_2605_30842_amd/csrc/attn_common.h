@@ -25,7 +25,6 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 constexpr int kWaves = 4;           // waves per workgroup
 constexpr int kThreads = 64 * kWaves;
 constexpr int kMaxGroup = 16;       // largest GQA group handled in one workgroup
-constexpr int kMergeBatch = 16;     // split partials loaded together by one thread in the merge
 constexpr float kLn2 = 0.69314718055994530942f;
 
 // Kernel arguments (passed by value). Offsets and strides are in bytes.
@@ -52,8 +51,9 @@ struct AttnParams {
   int32_t tail_chunk;  // work-queue form: tokens of each short last split, or 0 for none
   int32_t tail_splits; // work-queue form: short last splits per sequence (at most a quarter of its splits)
   float scale_log2;    // scale * log2(e)
-  uint32_t* tickets;   // [max_batch * Hkv] tickets, then 2 queue counters; zero between calls
+  uint32_t* tickets;   // [max_batch * Hkv] tickets 2^ticket_shift words apart, then 2 queue counters; zero between calls
   int32_t queue_slot;  // index of the queue counters in tickets
+  int32_t ticket_shift;
   float* lse_part;     // [B, Hkv, S, G]   (log2 units)
   float* o_part;       // [B, Hkv, S, G, D]
   const char* new_k;   // fused append: new rows [B, Hkv, D], or nullptr for attention only
@@ -201,15 +201,75 @@ struct MergeState {
   }
 };
 
+// Fold a lane's splits sub, sub + 2^ltps, ... of one output slot into its
+// running state. A batch of BATCH splits has its loads in flight together;
+// its largest log-weight is found first, so its part weights are independent
+// exponentials and its sums plain multiply-add chains, and the batch folds
+// into the state with one rescale. Each split part has weight sum 1 (it is
+// normalised) and log-weight lse2.
+template <int BATCH>
+__device__ inline void merge_parts(__amdgpu_buffer_rsrc_t rl, __amdgpu_buffer_rsrc_t ro, int log_group, int log_slots,
+                                   int ltps, int h, int slot, int sub, int nsplit_b, float& m, float& wsum,
+                                   float4& acc) {
+  const int last = nsplit_b - 1;
+#pragma unroll 1
+  for (int s0 = sub; s0 < nsplit_b; s0 += BATCH << ltps) {
+    float l2[BATCH];
+    float4 o[BATCH];
+#pragma unroll
+    for (int i = 0; i < BATCH; ++i) {
+      const int si = min(s0 + (i << ltps), last);  // past the last split: re-read it, weight 0
+      l2[i] = load_coherent(rl, ((si << log_group) + h) * 4);
+      o[i] = load4_coherent(ro, ((si << log_slots) + slot) * 16);
+    }
+    float mb = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < BATCH; ++i) {
+      if (s0 + (i << ltps) > last) l2[i] = -INFINITY;
+      mb = fmaxf(mb, l2[i]);
+    }
+    const float mn = fmaxf(m, mb);
+    const float ref = mn == -INFINITY ? 0.f : mn;
+    const float a = fast_exp2(m - ref);
+    acc = make_float4(acc.x * a, acc.y * a, acc.z * a, acc.w * a);
+    wsum *= a;
+#pragma unroll
+    for (int i = 0; i < BATCH; ++i) {
+      const float w = fast_exp2(l2[i] - ref);
+      wsum += w;
+      acc = make_float4(fmaf(w, o[i].x, acc.x), fmaf(w, o[i].y, acc.y), fmaf(w, o[i].z, acc.z),
+                        fmaf(w, o[i].w, acc.w));
+    }
+    m = mn;
+  }
+}
+
 // Merge the workgroup's wave states, write the split's result, and if this
 // split is the last of its (b, hk) to finish, merge all splits of (b, hk).
 // Must be called by every thread of the workgroup after a barrier that
 // follows the writes to `ws`.
+//
+// What bounds the end of a short call is not the partials' bytes but the
+// latency of this code, which every workgroup runs once and cold: after the
+// ticket, the loads of a 16-split merge took 0.25 us and the instructions
+// that computed their addresses 1.7 us. So indices are shifts (the group and
+// the head_dim are powers of two), a lane with at most 8 splits runs a merge
+// of 8 (with more, one of 16: a second round trip costs more than the longer
+// code), and what does not depend on the ticket is computed before it. With
+// the tickets on lines of their own, a batch-1 bf16 call (8 KV heads, G = 4,
+// D = 128) went from 8.0 to 6.7 us over 1024 tokens in 64-token splits, from
+// 14.1 to 12.1 us over 8192 in 256, and from 25.8 to 25.7 us over 32768 in
+// 1024.
 template <int D>
 __device__ void finalize_split(const AttnParams& p, const WaveState<D>& ws, int b, int hk, int j,
                                int nsplit_b) {
   __shared__ int sm_last;
+  constexpr int kLogRow = D == 128 ? 5 : 4;  // log2 of the slots of one head
+  static_assert(D == 4 << kLogRow, "a slot is 4 head_dim values");
   const int G = p.group;
+  const int log_group = __builtin_ctz(G);            // G is 1, 2, 4, 8 or 16
+  const int log_slots = log_group + kLogRow;
+  const int slots = 1 << log_slots;                  // slots of the group's G * D output values
   const int tid = threadIdx.x;
   const int head0 = b * p.num_q_heads + hk * G;  // first query head row of this (b, hk)
   const bool single = nsplit_b == 1;
@@ -217,11 +277,11 @@ __device__ void finalize_split(const AttnParams& p, const WaveState<D>& ws, int 
   // This (b, hk)'s partial results: lse [S][G] and outputs [S][G][D].
   const __amdgpu_buffer_rsrc_t rl = buffer_rsrc(p.lse_part + part0 * G, nsplit_b * G * 4);
   const __amdgpu_buffer_rsrc_t ro = buffer_rsrc(p.o_part + part0 * G * D, nsplit_b * G * D * 4);
-  const int slots = G * D / 4;  // 4 head_dim values per slot
+  float* out = p.out + static_cast<int64_t>(head0) * D;
 
   for (int slot = tid; slot < slots; slot += kThreads) {
-    const int h = (slot * 4) / D;
-    const int d0 = slot * 4 - h * D;
+    const int h = slot >> kLogRow;
+    const int d0 = (slot * 4) & (D - 1);
     MergeState st;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
@@ -234,72 +294,47 @@ __device__ void finalize_split(const AttnParams& p, const WaveState<D>& ws, int 
     const float lse2 = live ? st.m + log2f(st.wsum) : -INFINITY;
     if (single) {
       const float os = p.out_scale;
-      *reinterpret_cast<float4*>(p.out + static_cast<int64_t>(head0 + h) * D + d0) =
-          make_float4(on.x * os, on.y * os, on.z * os, on.w * os);
+      *reinterpret_cast<float4*>(out + slot * 4) = make_float4(on.x * os, on.y * os, on.z * os, on.w * os);
       if (d0 == 0 && p.lse != nullptr) p.lse[head0 + h] = live ? lse2 * kLn2 : -INFINITY;
     } else {
-      store4_coherent(ro, ((j * G + h) * D + d0) * 4, on);
+      store4_coherent(ro, (j * slots + slot) * 16, on);
       if (d0 == 0) store_coherent(rl, (j * G + h) * 4, lse2);
     }
   }
   if (single) return;
 
+  // Merge over splits. With fewer slots than threads, 2^ltps adjacent lanes
+  // share a slot, taking splits sub, sub + 2^ltps, ..., and then combine their
+  // states by lane shuffles. Every sum has a fixed order, so results do not
+  // depend on timing.
+  constexpr int kLogThreads = 8;
+  static_assert(kThreads == 1 << kLogThreads, "threads per workgroup");
+  const int ltps = log_slots >= kLogThreads ? 0 : kLogThreads - log_slots;
+  const int sub = tid & ((1 << ltps) - 1);
+  const int last = nsplit_b - 1;
+  uint32_t* ticket = p.tickets + (static_cast<int64_t>(b * p.num_kv_heads + hk) << p.ticket_shift);
+
   // Publish this split's partial result, then take a ticket.
   wait_stores_done();
   __syncthreads();
   if (tid == 0) {
-    const uint32_t prev = atomicAdd(&p.tickets[b * p.num_kv_heads + hk], 1u);
-    sm_last = prev == static_cast<uint32_t>(nsplit_b - 1);
+    const uint32_t prev = atomicAdd(ticket, 1u);
+    sm_last = prev == static_cast<uint32_t>(last);
   }
   __syncthreads();
   if (!sm_last) return;
 
-  // Merge over splits. With fewer slots than threads, tps adjacent lanes
-  // share a slot and take splits sub, sub + tps, ... Each lane visits its
-  // splits in batches of kMergeBatch whose loads are all in flight together;
-  // a batch's largest log-weight is found first, so its part weights are
-  // independent exponentials and its sums plain multiply-add chains, and the
-  // batch folds into the lane's running state with one rescale. The lanes of
-  // a slot then combine their states by lane shuffles. Every sum has a fixed
-  // order, so results do not depend on timing. Each split part has weight
-  // sum 1 (it is normalised) and log-weight lse2.
-  const int tps = slots >= kThreads ? 1 : kThreads / slots;
-  for (int slot = tid / tps; slot < slots; slot += kThreads / tps) {
-    const int sub = tid % tps;
-    const int h = (slot * 4) / D;
-    const int d0 = slot * 4 - h * D;
+  for (int slot = tid >> ltps; slot < slots; slot += kThreads >> ltps) {
+    const int h = slot >> kLogRow;
     float m = -INFINITY, wsum = 0.f;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int s0 = sub; s0 < nsplit_b; s0 += kMergeBatch * tps) {
-      float l2[kMergeBatch];
-      float4 o[kMergeBatch];
-#pragma unroll
-      for (int i = 0; i < kMergeBatch; ++i) {
-        const int si = min(s0 + i * tps, nsplit_b - 1);  // past the last split: re-read it, weight 0
-        l2[i] = load_coherent(rl, (si * G + h) * 4);
-        o[i] = load4_coherent(ro, ((si * G + h) * D + d0) * 4);
-      }
-      float mb = -INFINITY;
-#pragma unroll
-      for (int i = 0; i < kMergeBatch; ++i) {
-        if (s0 + i * tps >= nsplit_b) l2[i] = -INFINITY;
-        mb = fmaxf(mb, l2[i]);
-      }
-      const float mn = fmaxf(m, mb);
-      const float ref = mn == -INFINITY ? 0.f : mn;
-      const float a = fast_exp2(m - ref);
-      acc = make_float4(acc.x * a, acc.y * a, acc.z * a, acc.w * a);
-      wsum *= a;
-#pragma unroll
-      for (int i = 0; i < kMergeBatch; ++i) {
-        const float w = fast_exp2(l2[i] - ref);
-        wsum += w;
-        acc = make_float4(fmaf(w, o[i].x, acc.x), fmaf(w, o[i].y, acc.y), fmaf(w, o[i].z, acc.z),
-                          fmaf(w, o[i].w, acc.w));
-      }
-      m = mn;
+    if (nsplit_b <= 8 << ltps) {
+      merge_parts<8>(rl, ro, log_group, log_slots, ltps, h, slot, sub, nsplit_b, m, wsum, acc);
+    } else {
+      merge_parts<16>(rl, ro, log_group, log_slots, ltps, h, slot, sub, nsplit_b, m, wsum, acc);
     }
-    for (int off = 1; off < tps; off <<= 1) {
+#pragma unroll 1
+    for (int off = 1; off < 1 << ltps; off <<= 1) {
       MergeState st;
       st.m = m;
       st.wsum = wsum;
@@ -313,14 +348,13 @@ __device__ void finalize_split(const AttnParams& p, const WaveState<D>& ws, int 
     }
     if (sub == 0) {
       const float inv = p.out_scale / wsum;
-      *reinterpret_cast<float4*>(p.out + static_cast<int64_t>(head0 + h) * D + d0) =
-          make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
-      if (d0 == 0 && p.lse != nullptr) p.lse[head0 + h] = (m + log2f(wsum)) * kLn2;
+      *reinterpret_cast<float4*>(out + slot * 4) = make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
+      if ((slot & ((1 << kLogRow) - 1)) == 0 && p.lse != nullptr) p.lse[head0 + h] = (m + log2f(wsum)) * kLn2;
     }
   }
   // Back to zero for the next call. Issued after the merge's loads, which
   // would otherwise wait for it (memory operations complete in order).
-  if (tid == 0) atomicExch(&p.tickets[b * p.num_kv_heads + hk], 0u);
+  if (tid == 0) atomicExch(ticket, 0u);
 }
 
 }  // namespace comem

@@ -28,6 +28,7 @@ struct comem_decode_attn_plan {
   comem_decode_attn_config cfg;
   int device;
   int num_cus;
+  int ticket_shift;  // log2 of the words between two tickets
   size_t ticket_bytes;
   size_t workspace_bytes;
 };
