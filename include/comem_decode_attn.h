@@ -81,9 +81,11 @@ typedef enum {
 typedef enum {
   COMEM_VARIANT_AUTO = 0,     /* bf16, fp8 -> matrix-core kernel; f32 -> vector kernel */
   COMEM_VARIANT_VALU = 1,     /* vector-ALU kernel (f32 and bf16), one workgroup per split */
-  COMEM_VARIANT_MFMA = 2,     /* matrix-core kernel (bf16, fp8); persistent workgroups take
-                                 splits from a work queue when a workspace is given and
-                                 batch <= 4096, else one workgroup per split */
+  COMEM_VARIANT_MFMA = 2,     /* matrix-core kernel (bf16, fp8). With a workspace and batch <=
+                                 4096: long calls share all sequences' tokens out in equal
+                                 ranges, one per compute unit, and calls with a configured
+                                 chunk_tokens take their splits from a work queue. Otherwise,
+                                 and for short calls, one workgroup per split */
   COMEM_VARIANT_MFMA_GRID = 3 /* matrix-core kernel, always one workgroup per split */
 } comem_variant;
 
@@ -140,10 +142,13 @@ const char* comem_status_string(comem_status status);
  * entries of one split fit the matrix-core kernel's on-chip copy (2048
  * entries); a configured chunk_tokens that does not fit is refused with
  * COMEM_ERR_INVALID_SHAPE. A sequence of L tokens has ceil(L / chunk)
- * splits. When the matrix-core kernel's work queue has several rounds of
- * work items and the chunk was planned (chunk_tokens = 0), a sequence's last
- * splits are half a chunk each and the others up to 1.25 chunk; the split
- * boundaries depend only on L and the plan, so results stay reproducible. */
+ * splits, except that a matrix-core call with chunk_tokens = 0, a workspace
+ * of the size comem_decode_attn_init reports and either one sequence or a
+ * long bound (batch * max_ctx_len of a thousand tokens and more for every
+ * compute unit and sequence) cuts the tokens of all its sequences into equal
+ * ranges of whole 32-token tiles: the boundaries of a sequence's splits then
+ * follow from the lengths of all sequences in the call. Nothing depends on
+ * timing, so the same call always returns the same bits. */
 comem_status comem_decode_attn_plan_splits(const comem_decode_attn_plan* plan, int32_t batch,
                                            int64_t max_ctx_len, size_t workspace_bytes,
                                            int32_t* chunk_tokens_out, int32_t* num_splits_out);

@@ -19,7 +19,7 @@ using KernelFn = void (*)(AttnParams);
 using QueueKernelFn = void (*)(AttnParams, int);
 KernelFn select_mfma_kernel(int head_dim, bool paged, int page_size, bool fp8);
 QueueKernelFn select_mfma_queue_kernel(int head_dim, bool paged, int page_size, bool fp8);
-int mfma_max_split_pages();
+QueueKernelFn select_mfma_balanced_kernel(int head_dim, bool paged, int page_size, bool fp8);
 int mfma_max_queue_batch();
 KernelFn select_valu_kernel(bool bf16, int head_dim, int group, bool paged);
 }  // namespace comem
@@ -31,7 +31,9 @@ namespace {
 constexpr int kAssumedCUs = 256;                        // gfx950 (MI355X) without a device query
 constexpr int64_t kTargetWgsPerCu = 2;                  // workgroups per compute unit for one full round
 constexpr int kQueueWgsPerCu = 2;                       // resident workgroups per compute unit (MFMA kernel)
-constexpr int64_t kTailRounds = 4;                      // items per resident workgroup that enable short last splits
+constexpr int64_t kMinRangeTokens = 64;                 // shortest range of the balanced form
+constexpr int64_t kMaxBalancedTiles = int64_t{1} << 23; // 32-token tiles the balanced form counts exactly
+constexpr int64_t kMaxSplitPages = 2048;                // block-table entries of a configured split, upper bound
 constexpr int64_t kMinChunk = 64;                       // tokens per split, lower bound
 constexpr int64_t kMaxChunk = 2048;                     // tokens per split, upper bound (auto plan)
 
@@ -91,24 +93,82 @@ size_t call_workspace_bytes(const comem_decode_attn_plan& p, int64_t batch, int6
   return splits <= 1 ? 0 : slots_workspace_bytes(p, batch * splits);
 }
 
-// Tokens per split for the matrix-core kernel, from the host-side bounds of
-// a call (the device-side lengths are never read on the host). Splits of
+// Largest planned split, in tokens, of a paged call with pages of `page_size`
+// tokens (a multiple of 32): it spans no more entries than a configured one
+// may.
+int64_t mfma_page_cap(int64_t page_size) {
+  return std::max<int64_t>(32, (kMaxSplitPages - 2) * page_size / 32 * 32);
+}
+
+// Ranges of the balanced form (decode_mfma_balanced_kernel): one workgroup
+// per compute unit, `ranges` for each KV head. Above 32 KV heads that would
+// leave up to half the units idle, so two per unit there; one range (more
+// heads than workgroups) means no split at all.
+int64_t max_ranges(const comem_decode_attn_plan& p) {
+  const int64_t wgs = p.num_cus * (p.cfg.num_kv_heads > 32 ? 2 : 1);
+  return std::max<int64_t>(1, wgs / p.cfg.num_kv_heads);
+}
+
+// Workspace bytes of the balanced form past the tickets: two partial-result
+// slots per range and KV head.
+size_t balanced_bytes(const comem_decode_attn_plan& p) {
+  const size_t rows = 2 * static_cast<size_t>(max_ranges(p)) * static_cast<size_t>(p.cfg.num_q_heads);
+  return align256(rows * 4) + rows * static_cast<size_t>(p.cfg.head_dim) * 4;
+}
+
+// (Shortest piece worth a split, in 32-token tiles)^2 per tile of context
+// and sequence: with a us per token on one CU and m us per part to merge, a
+// length n splits best into pieces of sqrt(m n / a). From sweeps of batch-1
+// calls (us): a = 0.0045 + 1.1e-5 per byte of a token's K and V of one head
+// (0.0102 at 512 bytes, 0.006 at 256), m = 0.02 + 9e-5 per output value of
+// the group (0.065 at G D = 512, 0.2 at 2048).
+float split_coefficient(const comem_decode_attn_plan& p) {
+  const float token_bytes = 2.f * static_cast<float>(p.cfg.head_dim * elem_bytes(p.cfg));
+  const float a = 0.0045f + 1.1e-5f * token_bytes;
+  const float m = 0.02f + 9e-5f * static_cast<float>(group_of(p.cfg) * p.cfg.head_dim);
+  return m / (32.f * a);
+}
+
+// Tokens per split of a long call in the grid and work-queue forms, from the
+// host-side bounds (the device-side lengths are never read on the host). Splits of
 // 4096 tokens keep contexts of 128k and more at <= 32 splits; otherwise 2048
 // if that still leaves >= 16 work items per resident workgroup, else 1024.
 // Smaller items end the work queue more evenly (the last items handed out
 // finish at nearly the same time) at the cost of one more partial result
 // per item; at 8 items of 2048 tokens per workgroup the even end still wins.
-int64_t mfma_chunk(const comem_decode_attn_plan& p, int64_t batch, int64_t L) {
+int64_t long_chunk(const comem_decode_attn_plan& p, int64_t batch, int64_t L) {
   if (L >= 32 * 4096) return 4096;
   const int64_t resident = static_cast<int64_t>(kQueueWgsPerCu) * p.num_cus;
   if (batch * p.cfg.num_kv_heads * ceil_div(L, 2048) >= 16 * resident) return 2048;
   return 1024;
 }
 
-// Largest split, in tokens, whose block-table entries fit the matrix-core
-// kernel's LDS copy (a multiple of 32), for pages of `page_size` tokens.
-int64_t mfma_page_cap(int64_t page_size) {
-  return std::max<int64_t>(32, (comem::mfma_max_split_pages() - 2) * page_size / 32 * 32);
+// Long calls of several sequences take the balanced form, short ones one
+// workgroup per split. A range pays for every piece it holds with a merge
+// and a pipeline to refill (about 2048 tokens' worth of reading, and its
+// kernel starts 2 us later); the equal shares win that back once a range is
+// long. Measured (us, bf16, 8 KV heads, G = 4, lengths from a quarter of the
+// bound up, balanced / best splits): 8 x 16384 tokens 51.3 / 55.9, 16 x 8192
+// 51.7 / 57.6, 32 x 4096 53.4 / 59.3, 64 x 4096 114 / 132; on the other side
+// 8 x 8192 31.2 / 30.7, 64 x 1024 36.0 / 32.5, 128 x 1024 63.9 / 57.3, 128 x
+// 2048 124.6 / 120.9.
+bool long_call(const comem_decode_attn_plan& p, int64_t batch, int64_t L) {
+  const int64_t tokens = batch * p.cfg.num_kv_heads >= p.num_cus ? 2048 : 1024;
+  return batch * L >= tokens * (max_ranges(p) + batch);
+}
+
+// Tokens per split of a short call: one split per compute unit, none shorter
+// than a piece worth its merge; a whole sequence once the (sequence, head)
+// pairs fill the chip (64 x 1024 tokens: 32.5 us; 128 x 2048: 120.9, 126 at
+// 1024). Otherwise at most 1024: the bound may be far above the lengths, and
+// one longer split would run alone.
+int64_t short_chunk(const comem_decode_attn_plan& p, int64_t batch, int64_t L) {
+  const int64_t pairs = batch * p.cfg.num_kv_heads;
+  if (pairs >= p.num_cus) return ceil_div(L, 32) * 32;
+  const int64_t share = ceil_div(L, p.num_cus / pairs);
+  const double piece = 32.0 * std::sqrt(split_coefficient(p) * static_cast<double>(ceil_div(L, 32)));
+  const int64_t chunk = std::max({kMinRangeTokens, share, static_cast<int64_t>(std::ceil(piece))});
+  return std::min<int64_t>(1024, ceil_div(chunk, 32) * 32);
 }
 
 // Choose tokens per split and the split count for one call. page_size is 0
@@ -124,7 +184,10 @@ comem_status plan_call(const comem_decode_attn_plan& p, int64_t batch, int64_t m
     if (call_workspace_bytes(p, batch, ceil_div(L, chunk)) > ws_bytes) return COMEM_ERR_WORKSPACE_TOO_SMALL;
   } else {
     if (uses_mfma(p)) {
-      chunk = std::min(mfma_chunk(p, batch, L), cap);
+      const int64_t most = std::min(long_chunk(p, batch, L), cap);
+      chunk = long_call(p, batch, L) ? most : std::min(short_chunk(p, batch, L), cap);
+      // A workspace too small for these splits gets those of a long call.
+      if (call_workspace_bytes(p, batch, ceil_div(L, chunk)) > ws_bytes) chunk = std::max(chunk, most);
     } else {
       const int64_t target = kTargetWgsPerCu * p.num_cus;
       const int64_t per = ceil_div(batch * p.cfg.num_kv_heads * L, target);
@@ -184,6 +247,42 @@ bool uses_queue(const comem_decode_attn_plan& p, int64_t batch, const void* work
          workspace != nullptr && ws_bytes >= p.ticket_bytes;
 }
 
+// The balanced form of the matrix-core kernel: planned splits, a workspace
+// for its partial results, and a token count its 24-bit arithmetic holds.
+bool uses_balanced(const comem_decode_attn_plan& p, int64_t batch, int64_t max_ctx, const void* workspace,
+                   size_t ws_bytes, size_t ticket_region) {
+  return uses_mfma(p) && p.cfg.variant != COMEM_VARIANT_MFMA_GRID && p.cfg.chunk_tokens == 0 &&
+         (batch == 1 || long_call(p, batch, max_ctx)) && batch <= comem::mfma_max_queue_batch() &&
+         workspace != nullptr && ws_bytes >= ticket_region + balanced_bytes(p) && batch * ceil_div(max_ctx + 1, 32) < kMaxBalancedTiles;
+}
+
+comem_status launch_balanced(const comem_decode_attn_plan& p, bool paged, comem::AttnParams& a, int64_t batch,
+                             void* stream) {
+  // No more ranges than the call's bound can fill.
+  a.ranges = static_cast<int32_t>(
+      std::min(max_ranges(p), batch * ceil_div(std::max<int64_t>(a.max_ctx, 1), kMinRangeTokens)));
+  a.split_coef = split_coefficient(p) / static_cast<float>(batch);
+  const unsigned heads = static_cast<unsigned>(p.cfg.num_kv_heads), ranges = static_cast<unsigned>(a.ranges);
+  const int page = a.page_mask + 1;
+  hipError_t err;
+  if (batch == 1) {
+    comem::KernelFn fn = comem::select_mfma_kernel(p.cfg.head_dim, paged, page, is_fp8(p.cfg));
+    if (fn == nullptr) return COMEM_ERR_UNSUPPORTED;
+    a.num_splits = a.ranges;
+    void* args[] = {&a};
+    err = hipLaunchKernel(reinterpret_cast<const void*>(fn), dim3(ranges, heads), dim3(comem::kThreads), args, 0,
+                          static_cast<hipStream_t>(stream));
+  } else {
+    comem::QueueKernelFn fn = comem::select_mfma_balanced_kernel(p.cfg.head_dim, paged, page, is_fp8(p.cfg));
+    if (fn == nullptr) return COMEM_ERR_UNSUPPORTED;
+    int nb = static_cast<int>(batch);
+    void* args[] = {&a, &nb};
+    err = hipLaunchKernel(reinterpret_cast<const void*>(fn), dim3(heads, ranges), dim3(comem::kThreads), args, 0,
+                          static_cast<hipStream_t>(stream));
+  }
+  return err == hipSuccess ? COMEM_OK : COMEM_ERR_HIP;
+}
+
 comem_status launch(const comem_decode_attn_plan& p, bool paged, comem::AttnParams& a, int64_t batch,
                     int64_t splits, bool queue, void* stream) {
   const bool bf16 = p.cfg.dtype == COMEM_BF16;
@@ -191,20 +290,9 @@ comem_status launch(const comem_decode_attn_plan& p, bool paged, comem::AttnPara
   const int64_t resident = static_cast<int64_t>(kQueueWgsPerCu) * p.num_cus;
   // With no more (nominal) items than resident workgroups every item gets its
   // own workgroup anyway, and the grid form saves the queue's prologue.
-  if (queue && items > resident) {
+  if (queue && items > resident && (p.cfg.chunk_tokens > 0 || long_call(p, batch, a.max_ctx))) {
     comem::QueueKernelFn qfn = comem::select_mfma_queue_kernel(p.cfg.head_dim, paged, a.page_mask + 1, is_fp8(p.cfg));
     if (qfn == nullptr) return COMEM_ERR_UNSUPPORTED;
-    // With several rounds of items, each sequence ends in short splits of
-    // half a chunk, about one round of them in all: the queue hands them out
-    // last, so the workgroups finish closer together (quarter-chunk splits or
-    // two rounds of them gained less). Only planned chunks of 1024 tokens or
-    // more (and, paged, whose 1.25-chunk splits still fit the kernel's LDS
-    // copy of the block table); a configured chunk_tokens keeps even splits.
-    if (p.cfg.chunk_tokens == 0 && items >= kTailRounds * resident && a.chunk >= 1024 &&
-        (!paged || 2 * static_cast<int64_t>(a.chunk) <= mfma_page_cap(a.page_mask + 1))) {
-      a.tail_chunk = a.chunk / 2;
-      a.tail_splits = static_cast<int32_t>(ceil_div(resident, batch * p.cfg.num_kv_heads));
-    }
     dim3 grid(static_cast<unsigned>(items < resident ? items : resident));
     dim3 block(comem::kThreads);
     int nb = static_cast<int>(batch);
@@ -266,7 +354,7 @@ comem_status launch_append(const comem::AppendParams& a, bool paged, int32_t bat
 void fill_common(const comem_decode_attn_plan& p, comem::AttnParams& a, const void* q, const void* k,
                  const void* v, int64_t stride_token, int64_t stride_head, const int32_t* ctx_lens,
                  float* out, float* lse, void* workspace, int64_t batch, int64_t max_ctx_len, int64_t chunk,
-                 int64_t splits, bool queue, size_t ticket_region) {
+                 int64_t splits, bool queue, bool balanced, size_t ticket_region) {
   const int64_t e = elem_bytes(p.cfg);
   std::memset(&a, 0, sizeof(a));
   a.max_ctx = static_cast<int32_t>(max_ctx_len);
@@ -289,9 +377,10 @@ void fill_common(const comem_decode_attn_plan& p, comem::AttnParams& a, const vo
   a.out_scale = is_fp8(p.cfg) ? p.cfg.v_scale : 1.f;
   a.queue_slot = static_cast<int32_t>(counter_slot(p));
   a.ticket_shift = p.ticket_shift;
-  if (splits > 1 || queue) {
+  if (splits > 1 || queue || balanced) {
     char* ws = static_cast<char*>(workspace);
-    const size_t slots = static_cast<size_t>(batch) * static_cast<size_t>(splits) *
+    const size_t slots = (balanced ? 2 * static_cast<size_t>(max_ranges(p))
+                                   : static_cast<size_t>(batch) * static_cast<size_t>(splits)) *
                          static_cast<size_t>(p.cfg.num_q_heads);
     a.tickets = reinterpret_cast<uint32_t*>(ws);
     a.lse_part = reinterpret_cast<float*>(ws + ticket_region);
@@ -323,15 +412,17 @@ comem_status decode_contiguous(const comem_decode_attn_plan* plan, const void* q
   st = check_debug_workspace(*p, workspace, workspace_bytes);
   if (st != COMEM_OK) return st;
   if (p->device == COMEM_NO_DEVICE) return COMEM_ERR_NO_DEVICE;
+  const bool balanced = uses_balanced(*p, batch, max_ctx_len, workspace, workspace_bytes, ticket_region);
   const bool queue = uses_queue(*p, batch, workspace, workspace_bytes);
   comem::AttnParams a;
   fill_common(*p, a, q, k, v, stride_token, stride_head, ctx_lens, out, lse, workspace, batch, max_ctx_len, chunk,
-              splits, queue, ticket_region);
+              splits, queue, balanced, ticket_region);
   a.seq_start = seq_start;
   if (fused) {
     a.new_k = static_cast<const char*>(new_k);
     a.new_v = static_cast<const char*>(new_v);
   }
+  if (balanced) return launch_balanced(*p, false, a, batch, hip_stream);
   return launch(*p, false, a, batch, splits, queue, hip_stream);
 }
 
@@ -355,16 +446,17 @@ comem_status decode_paged(const comem_decode_attn_plan* plan, const void* q, con
   int64_t chunk = 0, splits = 0;
   st = plan_call(*p, batch, max_ctx_len, page_size, workspace == nullptr ? 0 : workspace_bytes, &chunk, &splits);
   if (st != COMEM_OK) return st;
-  // The matrix-core kernel stages one split's block-table entries in LDS (a
-  // planned split always fits; a configured chunk_tokens may not).
-  if (uses_mfma(*p) && (chunk - 1) / page_size + 2 > comem::mfma_max_split_pages()) return COMEM_ERR_INVALID_SHAPE;
+  // A split's block-table entries are bounded (a planned split always fits; a
+  // configured chunk_tokens may not).
+  if (uses_mfma(*p) && (chunk - 1) / page_size + 2 > kMaxSplitPages) return COMEM_ERR_INVALID_SHAPE;
   st = check_debug_workspace(*p, workspace, workspace_bytes);
   if (st != COMEM_OK) return st;
   if (p->device == COMEM_NO_DEVICE) return COMEM_ERR_NO_DEVICE;
+  const bool balanced = uses_balanced(*p, batch, max_ctx_len, workspace, workspace_bytes, p->ticket_bytes);
   const bool queue = uses_queue(*p, batch, workspace, workspace_bytes);
   comem::AttnParams a;
   fill_common(*p, a, q, k_pages, v_pages, stride_token, stride_head, ctx_lens, out, lse, workspace, batch,
-              max_ctx_len, chunk, splits, queue, p->ticket_bytes);
+              max_ctx_len, chunk, splits, queue, balanced, p->ticket_bytes);
   a.block_table = block_table;
   a.stride_page = stride_page * elem_bytes(p->cfg);
   a.max_pages = max_pages_per_seq;
@@ -375,6 +467,7 @@ comem_status decode_paged(const comem_decode_attn_plan* plan, const void* q, con
     a.new_k = static_cast<const char*>(new_k);
     a.new_v = static_cast<const char*>(new_v);
   }
+  if (balanced) return launch_balanced(*p, true, a, batch, hip_stream);
   return launch(*p, true, a, batch, splits, queue, hip_stream);
 }
 
@@ -433,7 +526,7 @@ comem_status comem_decode_attn_init(const comem_decode_attn_config* cfg, int dev
   if (cfg->chunk_tokens > 0) {
     slots = B * ceil_div(L, cfg->chunk_tokens);
   } else if (uses_mfma(*p)) {
-    slots = B * ceil_div(L, 1024);
+    slots = std::max(B * ceil_div(L, 1024), ceil_div(static_cast<int64_t>(p->num_cus), cfg->num_kv_heads));
   } else {
     const int64_t target = kTargetWgsPerCu * p->num_cus;
     const int64_t a = ceil_div(target, cfg->num_kv_heads) + B;
@@ -443,6 +536,8 @@ comem_status comem_decode_attn_init(const comem_decode_attn_config* cfg, int dev
     if (c < slots) slots = c;
   }
   p->workspace_bytes = slots_workspace_bytes(*p, slots);
+  if (cfg->chunk_tokens == 0 && uses_mfma(*p) && cfg->variant != COMEM_VARIANT_MFMA_GRID)
+    p->workspace_bytes = std::max(p->workspace_bytes, p->ticket_bytes + balanced_bytes(*p));
   // The allocation-free entry point's scratch on this device (looked up and
   // cleared once per device); the other entry points work without it.
   if (device != COMEM_NO_DEVICE) (void)comem::scratch_setup(device);
@@ -524,6 +619,10 @@ comem_status comem_decode_attn_noalloc(const comem_decode_attn_plan* plan, const
   int64_t chunk = 0, splits = 0;
   st = plan_call(*p, batch, max_ctx_len, 0, p->workspace_bytes, &chunk, &splits);
   if (st != COMEM_OK) return st;
+  // (A short call's splits never need more than those of 1024 tokens and up
+  // that decide here.)
+  if (uses_mfma(*p) && p->cfg.chunk_tokens == 0)
+    splits = std::max(splits, ceil_div(max_ctx_len > 0 ? max_ctx_len : 1, long_chunk(*p, batch, max_ctx_len)));
   const size_t partials = call_workspace_bytes(*p, batch, splits);
   const size_t need = comem::kScratchTicketBytes + (partials > 0 ? partials - p->ticket_bytes : 0);
   if (need > comem::kScratchBytes) return COMEM_ERR_SCRATCH_LIMIT;

@@ -48,14 +48,14 @@ struct AttnParams {
   int32_t group;       // G = Hq / Hkv
   int32_t chunk;       // tokens per split (multiple of 32)
   int32_t num_splits;  // most splits of one sequence (the stride of the partial results)
-  int32_t tail_chunk;  // work-queue form: tokens of each short last split, or 0 for none
-  int32_t tail_splits; // work-queue form: short last splits per sequence (at most a quarter of its splits)
+  int32_t ranges;      // balanced form: equal ranges of the call's tokens, else 0
+  float split_coef;    // balanced form: (shortest piece in 32-token tiles)^2 / tiles of the call
   float scale_log2;    // scale * log2(e)
   uint32_t* tickets;   // [max_batch * Hkv] tickets 2^ticket_shift words apart, then 2 queue counters; zero between calls
   int32_t queue_slot;  // index of the queue counters in tickets
   int32_t ticket_shift;
-  float* lse_part;     // [B, Hkv, S, G]   (log2 units)
-  float* o_part;       // [B, Hkv, S, G, D]
+  float* lse_part;     // [B, Hkv, S, G] (log2 units); balanced form: [Hkv, 2 * ranges, G]
+  float* o_part;       // [B, Hkv, S, G, D]; balanced form: [Hkv, 2 * ranges, G, D]
   const char* new_k;   // fused append: new rows [B, Hkv, D], or nullptr for attention only
   const char* new_v;
   int64_t num_pages;   // paged layout: pool size (bounds every page access)
@@ -119,6 +119,21 @@ __device__ inline int64_t row_offset(const AttnParams& p, int b, int64_t seq0, i
 }
 
 __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+
+// p0, p1 -> (hi, lo) bf16 pairs with p = hi + lo to about 2^-18 relative: hi
+// is the value rounded to nearest even, lo the exact fp32 remainder, rounded
+// likewise. (With hi truncated instead, lo is twice as large and so is the
+// error: over 131072 tokens in 32768-token splits the outputs were off by
+// 4.7e-6 of their norm, now 2.4e-6; the conversions are instructions of their
+// own, so this costs less than rounding lo by hand.)
+__device__ inline void split_bf16(float p0, float p1, uint32_t& hi, uint32_t& lo) {
+  hi = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t{p0, p1}), bf16x2_t));
+  const f32x2_t r = {p0 - __uint_as_float(hi << 16), p1 - __uint_as_float(hi & 0xffff0000u)};
+  lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2_t));
+}
 
 // Fused KV append (paper Sec. 2.2: the new token's key and value join the
 // caches before it attends). Called by the one wave of the split holding
@@ -201,13 +216,42 @@ struct MergeState {
   }
 };
 
+// Where the partial results of one (b, hk) lie: split i at slot
+// first_slot + slot_of(i), of `count` splits, of which the workgroup holds
+// split j.
+//
+// Even splits of `chunk` tokens: one slot per split, p.num_splits per (b, hk).
+struct EvenParts {
+  int64_t first_slot;
+  int j, count;
+  static __device__ int splits(int L, int chunk) { return L > 0 ? 1 + (L - 1) / chunk : 1; }
+  __device__ EvenParts(const AttnParams& p, int b, int hk, int split, int L, int chunk)
+      : first_slot((static_cast<int64_t>(b) * p.num_kv_heads + hk) * p.num_splits), j(split), count(splits(L, chunk)) {}
+  static __device__ int slot_of(int i) { return i; }
+  __device__ int slots() const { return count; }
+};
+
+// Balanced ranges: two slots per (hk, range), since at most two of a range's
+// pieces belong to sequences it shares with other ranges: slot 0 for the
+// piece of a sequence that began in an earlier range, slot 1 for one that
+// begins in it. A sequence over ranges r0 .. r1 so has its splits at slots
+// 1, 2, 4, 6, ... from range r0's first slot on.
+struct RangeParts {
+  int64_t first_slot;
+  int j, count;
+  __device__ RangeParts(const AttnParams& p, int hk, int r, int r0, int r1)
+      : first_slot(2 * (static_cast<int64_t>(hk) * p.ranges + r0)), j(r - r0), count(r1 - r0 + 1) {}
+  static __device__ int slot_of(int i) { return max(2 * i, 1); }
+  __device__ int slots() const { return 2 * count; }
+};
+
 // Fold a lane's splits sub, sub + 2^ltps, ... of one output slot into its
 // running state. A batch of BATCH splits has its loads in flight together;
 // its largest log-weight is found first, so its part weights are independent
 // exponentials and its sums plain multiply-add chains, and the batch folds
 // into the state with one rescale. Each split part has weight sum 1 (it is
 // normalised) and log-weight lse2.
-template <int BATCH>
+template <int BATCH, typename Parts>
 __device__ inline void merge_parts(__amdgpu_buffer_rsrc_t rl, __amdgpu_buffer_rsrc_t ro, int log_group, int log_slots,
                                    int ltps, int h, int slot, int sub, int nsplit_b, float& m, float& wsum,
                                    float4& acc) {
@@ -218,7 +262,7 @@ __device__ inline void merge_parts(__amdgpu_buffer_rsrc_t rl, __amdgpu_buffer_rs
     float4 o[BATCH];
 #pragma unroll
     for (int i = 0; i < BATCH; ++i) {
-      const int si = min(s0 + (i << ltps), last);  // past the last split: re-read it, weight 0
+      const int si = Parts::slot_of(min(s0 + (i << ltps), last));  // past the last split: re-read it, weight 0
       l2[i] = load_coherent(rl, ((si << log_group) + h) * 4);
       o[i] = load4_coherent(ro, ((si << log_slots) + slot) * 16);
     }
@@ -260,9 +304,8 @@ __device__ inline void merge_parts(__amdgpu_buffer_rsrc_t rl, __amdgpu_buffer_rs
 // D = 128) went from 8.0 to 6.7 us over 1024 tokens in 64-token splits, from
 // 14.1 to 12.1 us over 8192 in 256, and from 25.8 to 25.7 us over 32768 in
 // 1024.
-template <int D>
-__device__ void finalize_split(const AttnParams& p, const WaveState<D>& ws, int b, int hk, int j,
-                               int nsplit_b) {
+template <int D, typename Parts>
+__device__ void finalize_split(const AttnParams& p, const WaveState<D>& ws, int b, int hk, const Parts& parts) {
   __shared__ int sm_last;
   constexpr int kLogRow = D == 128 ? 5 : 4;  // log2 of the slots of one head
   static_assert(D == 4 << kLogRow, "a slot is 4 head_dim values");
@@ -272,11 +315,12 @@ __device__ void finalize_split(const AttnParams& p, const WaveState<D>& ws, int 
   const int slots = 1 << log_slots;                  // slots of the group's G * D output values
   const int tid = threadIdx.x;
   const int head0 = b * p.num_q_heads + hk * G;  // first query head row of this (b, hk)
+  const int nsplit_b = parts.count;
   const bool single = nsplit_b == 1;
-  const int64_t part0 = (static_cast<int64_t>(b) * p.num_kv_heads + hk) * p.num_splits;
-  // This (b, hk)'s partial results: lse [S][G] and outputs [S][G][D].
-  const __amdgpu_buffer_rsrc_t rl = buffer_rsrc(p.lse_part + part0 * G, nsplit_b * G * 4);
-  const __amdgpu_buffer_rsrc_t ro = buffer_rsrc(p.o_part + part0 * G * D, nsplit_b * G * D * 4);
+  // This (b, hk)'s partial results: lse [slots][G] and outputs [slots][G][D].
+  const int part = Parts::slot_of(parts.j);
+  const __amdgpu_buffer_rsrc_t rl = buffer_rsrc(p.lse_part + parts.first_slot * G, parts.slots() * G * 4);
+  const __amdgpu_buffer_rsrc_t ro = buffer_rsrc(p.o_part + parts.first_slot * G * D, parts.slots() * G * D * 4);
   float* out = p.out + static_cast<int64_t>(head0) * D;
 
   for (int slot = tid; slot < slots; slot += kThreads) {
@@ -297,8 +341,8 @@ __device__ void finalize_split(const AttnParams& p, const WaveState<D>& ws, int 
       *reinterpret_cast<float4*>(out + slot * 4) = make_float4(on.x * os, on.y * os, on.z * os, on.w * os);
       if (d0 == 0 && p.lse != nullptr) p.lse[head0 + h] = live ? lse2 * kLn2 : -INFINITY;
     } else {
-      store4_coherent(ro, (j * slots + slot) * 16, on);
-      if (d0 == 0) store_coherent(rl, (j * G + h) * 4, lse2);
+      store4_coherent(ro, (part * slots + slot) * 16, on);
+      if (d0 == 0) store_coherent(rl, (part * G + h) * 4, lse2);
     }
   }
   if (single) return;
@@ -329,9 +373,9 @@ __device__ void finalize_split(const AttnParams& p, const WaveState<D>& ws, int 
     float m = -INFINITY, wsum = 0.f;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     if (nsplit_b <= 8 << ltps) {
-      merge_parts<8>(rl, ro, log_group, log_slots, ltps, h, slot, sub, nsplit_b, m, wsum, acc);
+      merge_parts<8, Parts>(rl, ro, log_group, log_slots, ltps, h, slot, sub, nsplit_b, m, wsum, acc);
     } else {
-      merge_parts<16>(rl, ro, log_group, log_slots, ltps, h, slot, sub, nsplit_b, m, wsum, acc);
+      merge_parts<16, Parts>(rl, ro, log_group, log_slots, ltps, h, slot, sub, nsplit_b, m, wsum, acc);
     }
 #pragma unroll 1
     for (int off = 1; off < 1 << ltps; off <<= 1) {

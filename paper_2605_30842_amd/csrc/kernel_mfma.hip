@@ -1,16 +1,16 @@
 // Matrix-core (MFMA) decode-attention kernel for bf16 caches on gfx950.
 //
-// One work item = one (split j, KV head hk, sequence b), run by one
-// workgroup: in the grid form one workgroup per item, in the work-queue form
-// persistent workgroups that take items from a queue. The 4 waves take
-// 32-token tiles of the split in turn. Per tile a wave computes
+// One work item = one (split, KV head hk, sequence b), run by one workgroup.
+// Three forms hand the items out: one workgroup per split (short calls), equal
+// ranges over all sequences' tokens (long calls), and a queue (configured
+// split sizes). The 4 waves take 32-token tiles of the split in turn. Per tile a wave computes
 //   S^T[token, head] = K_tile . Q^T    with v_mfma_f32_16x16x32_bf16
 // (16 tokens x 16 head columns per instruction; the G real heads of the GQA
 // group occupy the first G columns), runs the online softmax on the scores
 // in registers, and accumulates
 //   O[head, d] += P[head, token] . V_tile[token, d]
 // again with 16x16x32 MFMAs. P is split as P = P_hi + P_lo, both bf16, and
-// both halves are multiplied (two MFMAs), so the weights keep about 16
+// both halves are multiplied (two MFMAs), so the weights keep about 17
 // significant bits instead of bf16's 8.
 //
 // Operand layouts (lane = 16 * g + c, c in 0..15, g in 0..3):
@@ -61,16 +61,16 @@ template <>
 struct VRow<128> {
   u32x4 w;
   __device__ uint32_t word(int i) const { return w[i]; }
-  __device__ void load(__amdgpu_buffer_rsrc_t r, uint32_t voff, int soff) {
-    w = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, kStreaming));
+  __device__ void load(__amdgpu_buffer_rsrc_t r, uint32_t voff) {
+    w = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, 0, kStreaming));
   }
 };
 template <>
 struct VRow<64> {
   u32x2 w;
   __device__ uint32_t word(int i) const { return w[i]; }
-  __device__ void load(__amdgpu_buffer_rsrc_t r, uint32_t voff, int soff) {
-    w = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, kStreaming));
+  __device__ void load(__amdgpu_buffer_rsrc_t r, uint32_t voff) {
+    w = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(r, voff, 0, kStreaming));
   }
 };
 
@@ -89,15 +89,15 @@ struct VRow8;
 template <>
 struct VRow8<128> {
   u32x2 w;
-  __device__ void load(__amdgpu_buffer_rsrc_t r, uint32_t voff, int soff) {
-    w = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, kStreaming));
+  __device__ void load(__amdgpu_buffer_rsrc_t r, uint32_t voff) {
+    w = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(r, voff, 0, kStreaming));
   }
 };
 template <>
 struct VRow8<64> {
   uint32_t w;
-  __device__ void load(__amdgpu_buffer_rsrc_t r, uint32_t voff, int soff) {
-    w = __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, kStreaming);
+  __device__ void load(__amdgpu_buffer_rsrc_t r, uint32_t voff) {
+    w = __builtin_amdgcn_raw_buffer_load_b32(r, voff, 0, kStreaming);
   }
 };
 
@@ -147,10 +147,8 @@ __device__ inline void widen_tile(const Tile8<D>& R, Tile<D>& T) {
   }
 }
 
-// Page lookups of one split go through LDS: the workgroup copies the split's
-// block-table entries there once, so the token loop never waits on them.
-constexpr int kMaxSplitPages = 2048;
-// Largest batch the work-queue kernel takes (its per-sequence split offsets live in LDS).
+// Largest batch the work-queue and the balanced kernel take (their
+// per-sequence offsets live in LDS).
 constexpr int kMaxQueueBatch = 4096;
 
 enum class Layout { kContig, kPaged, kPagedFine };
@@ -161,78 +159,140 @@ struct Loader {
   static constexpr int kElemBytes = FP8 ? 1 : 2;
   const char* kbase;  // K of this (b, hk): contiguous layout already offset to the sequence start
   const char* vbase;
-  const int32_t* sm_pages;  // LDS copy of the split's block-table entries (paged layouts)
-  int page_first;           // token index of the first entry in sm_pages
-  int64_t stride_token;
+  const int32_t* bt_row;  // the sequence's block-table row (paged layouts)
+  uint32_t pool;          // pages in the pool; an entry at or past it (negative ones too) is outside
+  uint32_t* errors;
+  uint32_t stride_token;  // at most 2^26
   int64_t stride_page;
   int page_shift, page_mask;
+  int t_first;  // the wave's first tile
   int t_end;
-  int c, g;
-  uint32_t koff;  // c * stride_token + 16 g (FP8: + (D / 4) g)
-  uint32_t voff;  // 4 g * stride_token + (NT * c elements)
+  int lane, c, g;
+  uint32_t koff;     // c * stride_token + 16 g (FP8: + (D / 4) g)
+  uint32_t voff[4];  // (4 g + r) * stride_token + (NT * c elements)
 
-  // Byte offset of token t from the base; uniform across the wave when t is.
-  __device__ int64_t token_offset(int t) const {
-    if constexpr (LAYOUT == Layout::kContig) {
-      return static_cast<int64_t>(t) * stride_token;
+  // Block-table entries. They come as vector loads, requested well ahead of
+  // the tiles that need them, and take no LDS and no barrier. (As scalar
+  // loads they shared the counter of the cross-lane maximum's LDS
+  // operations, which then waited for them: 8 x 131072 tokens took 661
+  // instead of 630 us.)
+  //
+  // Pages of 16 tokens or more: lane l of `now` holds the entry of half l % 2
+  // of the wave's tile 32 i + l / 2, that of `next` the entries of the 32
+  // tiles after those. Smaller pages: lane l < 32 of `now` holds the entry of
+  // token l of the tile to be requested, `next` those of the tile after it.
+  int32_t now, next;
+
+  // An entry outside the pool reads page 0.
+  __device__ int32_t in_pool(int32_t entry) const {
+    if (static_cast<uint32_t>(entry) >= pool) {
+      if (errors != nullptr) atomicOr(errors, kErrBlockTable);
+      return 0;
+    }
+    return entry;
+  }
+  __device__ int32_t entry_of(int t) const { return bt_row[min(t, t_end - 1) >> page_shift]; }
+  // Entries of the wave's tiles n .. n + 31 (n a multiple of 32), or of its tile n.
+  __device__ int32_t entries(int n) const {
+    if constexpr (LAYOUT == Layout::kPaged) return entry_of(t_first + 32 * kWaves * (n + (lane >> 1)) + 16 * (lane & 1));
+    return entry_of(t_first + 32 * kWaves * n + (lane & 31));
+  }
+  __device__ void first_entries() {
+    if constexpr (LAYOUT == Layout::kPaged) {
+      now = in_pool(entries(0));
+      next = entries(32);
+    } else if constexpr (LAYOUT == Layout::kPagedFine) {
+      now = entries(0);
+      next = entries(1);
+    }
+  }
+  // t tokens, in bytes (t >= 0).
+  __device__ int64_t tokens(int t) const {
+    return static_cast<int64_t>(static_cast<uint64_t>(static_cast<uint32_t>(t)) * stride_token);
+  }
+
+  // Before the request of the wave's tile n (n = 1, 2, ...).
+  __device__ void next_entries(int n) {
+    if constexpr (LAYOUT == Layout::kPaged) {
+      if ((n & 31) == 0) {
+        now = in_pool(next);
+        next = entries(n + 32);
+      }
+    } else if constexpr (LAYOUT == Layout::kPagedFine) {
+      now = next;
+      next = entries(n + 1);
+    }
+  }
+
+  // Request the wave's tile n, at token t0. Contiguous caches and pages of 16
+  // tokens or more: per 16-token half one buffer descriptor on the half's
+  // first row (uniform, in SGPRs) and fixed 32-bit lane offsets. The
+  // descriptor ends with the last row inside the split, so rows past it
+  // arrive as zeros without a memory access; their weights are zero. Smaller
+  // pages: per-lane rows, clamped to the last valid one. With `repeat` the
+  // call only keeps the load count of the pipeline steady: it re-reads the
+  // tile's K rows (still cached) into both halves and its data is unused.
+  __device__ void load(TileT& T, int n, int t0, bool repeat) const {
+    constexpr int KB = D / 32;
+    const char* vsrc = repeat ? kbase : vbase;
+    if constexpr (LAYOUT == Layout::kPagedFine) {
+      constexpr int VBYTES = kElemBytes * D / 16;
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const char* kr = kbase + lane_row(t0, 16 * s + c) + (FP8 ? (D / 4) * g : 16 * g);
+        if constexpr (FP8) {
+#pragma unroll
+          for (int i = 0; i < D / 64; ++i) T.k[s][i] = *reinterpret_cast<const u32x4*>(kr + 16 * i);
+        } else {
+#pragma unroll
+          for (int kk = 0; kk < KB; ++kk) T.k[s][kk] = *reinterpret_cast<const u32x4*>(kr + 64 * kk);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          T.v[s][r].w = *reinterpret_cast<const decltype(T.v[s][r].w)*>(vsrc + lane_row(t0, 16 * s + 4 * g + r) + VBYTES * c);
+      }
     } else {
-      const int page = max(0, sm_pages[(t - page_first) >> page_shift]);  // -1 (outside the pool) reads page 0
-      return static_cast<int64_t>(page) * stride_page + static_cast<int64_t>(t & page_mask) * stride_token;
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const int t = t0 + 16 * s;
+        int64_t base;
+        if constexpr (LAYOUT == Layout::kContig) {
+          base = tokens(t);
+        } else {
+          const int page = __builtin_amdgcn_readlane(now, 2 * (n & 31) + s);
+          base = static_cast<int64_t>(page) * stride_page + tokens(t & page_mask);
+        }
+        base = uniform_i64(base);
+        // Bytes from the half's first row to the end of its last one inside
+        // the split (selects, not a clamp: the clamp became a vector
+        // instruction whose register waited for tile loads in flight).
+        const int left = t_end - t;
+        const uint32_t some = left > 0 ? (static_cast<uint32_t>(left) - 1) * stride_token + kElemBytes * D : 0;
+        const int extent = uniform_i32(static_cast<int>(left >= 16 ? 15 * stride_token + kElemBytes * D : some));
+        const __amdgpu_buffer_rsrc_t rk =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(kbase + base), 0, extent, kBufferConfig);
+        const __amdgpu_buffer_rsrc_t rv =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(vsrc + base), 0, extent, kBufferConfig);
+        if constexpr (FP8) {
+#pragma unroll
+          for (int i = 0; i < D / 64; ++i)
+            T.k[s][i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rk, koff + 16 * i, 0, 0));
+        } else {
+#pragma unroll
+          for (int kk = 0; kk < KB; ++kk)
+            T.k[s][kk] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rk, koff + 64 * kk, 0, 0));
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) T.v[s][r].load(rv, voff[r]);
+      }
     }
   }
 
-  // A full 32-token tile whose 16-token halves each lie in one page (or the
-  // contiguous layout): per half, one buffer descriptor on the half's first
-  // row (uniform, in SGPRs) and fixed 32-bit lane offsets. The descriptor's
-  // size covers exactly the 16 rows, so the hardware returns zeros instead of
-  // touching memory should an offset ever fall outside them. With `repeat`
-  // the call only keeps the load count of the pipeline steady: it re-reads
-  // the tile's K rows (still cached) into both halves and its data is unused.
-  __device__ void load_full(TileT& T, int t0, bool repeat) const {
-    constexpr int KB = D / 32;
-    const int extent = static_cast<int>(15 * stride_token + kElemBytes * D);
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int64_t base = uniform_i64(token_offset(t0 + 16 * s));
-      const __amdgpu_buffer_rsrc_t rk =
-          __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(kbase + base), 0, extent, kBufferConfig);
-      const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(
-          const_cast<char*>((repeat ? kbase : vbase) + base), 0, extent, kBufferConfig);
-      if constexpr (FP8) {
-#pragma unroll
-        for (int i = 0; i < D / 64; ++i)
-          T.k[s][i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rk, koff + 16 * i, 0, 0));
-      } else {
-#pragma unroll
-        for (int kk = 0; kk < KB; ++kk)
-          T.k[s][kk] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rk, koff + 64 * kk, 0, 0));
-      }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) T.v[s][r].load(rv, voff, static_cast<int>(r * stride_token));
-    }
-  }
-
-  // Any tile: per-lane rows; tokens past the end are clamped to the last
-  // valid row (their weight is zero), so no byte outside a context is read.
-  __device__ void load_any(TileT& T, int t0) const {
-    constexpr int KB = D / 32;
-    constexpr int VBYTES = kElemBytes * D / 16;
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const char* kr = kbase + token_offset(min(t0 + 16 * s + c, t_end - 1)) + (FP8 ? (D / 4) * g : 16 * g);
-      if constexpr (FP8) {
-#pragma unroll
-        for (int i = 0; i < D / 64; ++i) T.k[s][i] = *reinterpret_cast<const u32x4*>(kr + 16 * i);
-      } else {
-#pragma unroll
-        for (int kk = 0; kk < KB; ++kk) T.k[s][kk] = *reinterpret_cast<const u32x4*>(kr + 64 * kk);
-      }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const char* vr = vbase + token_offset(min(t0 + 16 * s + 4 * g + r, t_end - 1)) + VBYTES * c;
-        T.v[s][r].w = *reinterpret_cast<const decltype(T.v[s][r].w)*>(vr);
-      }
-    }
+  // Small pages: byte offset of row i of the tile at t0, clamped to the last valid one.
+  __device__ int64_t lane_row(int t0, int i) const {
+    const int ic = min(i, t_end - 1 - t0);
+    return static_cast<int64_t>(in_pool(__shfl(now, ic))) * stride_page +
+           tokens((t0 + ic) & page_mask);
   }
 };
 
@@ -284,14 +344,7 @@ __device__ inline void compute_tile(const Tile<D>& T, int t0, int t_end, int g,
     const float p0 = fast_exp2(x[e] - m_new);
     const float p1 = fast_exp2(x[e + 1] - m_new);
     psum += p0 + p1;
-    const uint32_t b0 = __float_as_uint(p0), b1 = __float_as_uint(p1);
-    ph[e / 2] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);  // upper halves: truncated bf16
-    // remainders p - hi are exact in fp32; round them to nearest-even bf16
-    uint32_t r0 = __float_as_uint(p0 - __uint_as_float(b0 & 0xffff0000u));
-    uint32_t r1 = __float_as_uint(p1 - __uint_as_float(b1 & 0xffff0000u));
-    r0 += 0x7fffu + ((r0 >> 16) & 1u);
-    r1 += 0x7fffu + ((r1 >> 16) & 1u);
-    pl[e / 2] = __builtin_amdgcn_perm(r1, r0, 0x07060302u);
+    split_bf16(p0, p1, ph[e / 2], pl[e / 2]);
   }
   l_run = l_run * alpha + psum;
   const bf16x8 pa_hi = as_bf16x8(u32x4{ph[0], ph[1], ph[2], ph[3]});
@@ -336,71 +389,21 @@ __device__ inline void load_sequence(const AttnParams& p, int b, int& L, int64_t
   L = checked_len(L, p.max_ctx, p.errors);
 }
 
-// Shared memory of one workgroup; the page table and the wave states are
-// rewritten for every split the workgroup processes.
-template <int D, Layout LAYOUT>
-struct SplitSmem {
-  WaveState<D> ws;
-  int32_t pages[LAYOUT == Layout::kContig ? 1 : kMaxSplitPages];
-};
-
-// The splits of a sequence of L tokens in the work-queue form. There are
-// ceil(L / chunk) of them (one, empty, when L = 0), normally split j = tokens
-// [j * chunk, min((j + 1) * chunk, L)), as in the grid form. With short last
-// splits (tail_chunk > 0), the last `small` splits, at most a quarter of
-// them, cover tail_chunk tokens each (the very last one up to L) and start
-// at a multiple of 32; the others share the tokens before them evenly in
-// whole 32-token tiles (the first `rem` of them one tile more), so no split
-// exceeds 1.25 chunk. The queue hands out every sequence's large splits
-// before any short one, so the items taken last are short and workgroups
-// finish close together. The ranges depend on L and the plan only, never on
-// which workgroup runs them or when.
-struct SplitGeometry {
-  int nsplit;       // splits of the sequence
-  int small;        // short last splits among them
-  int small_start;  // first token of the short splits (L without them)
-  int q, rem;       // large split j has q tiles, one more if j < rem
-
-  __device__ SplitGeometry(int L, const AttnParams& p) {
-    nsplit = L > 0 ? 1 + (L - 1) / p.chunk : 1;
-    small = p.tail_chunk > 0 ? min(p.tail_splits, nsplit / 4) : 0;
-    small_start = small > 0 ? (L - small * p.tail_chunk) & ~31 : L;
-    const int tiles = small_start >> 5;
-    q = small > 0 ? tiles / (nsplit - small) : 0;
-    rem = small > 0 ? tiles - q * (nsplit - small) : 0;
-  }
-  __device__ int big() const { return nsplit - small; }
-
-  // Tokens [t0, t1) of split j < nsplit.
-  __device__ void range(int j, int L, const AttnParams& p, int& t0, int& t1) const {
-    if (small == 0) {
-      t0 = j * p.chunk;
-      t1 = t0 + min(L - t0, p.chunk);
-    } else if (j < big()) {
-      t0 = 32 * (j * q + min(j, rem));
-      t1 = t0 + 32 * (q + (j < rem ? 1 : 0));
-    } else {
-      const int s = j - big();
-      t0 = small_start + s * p.tail_chunk;
-      t1 = s == small - 1 ? L : t0 + p.tail_chunk;
-    }
-  }
-};
-
-// Attention of the G query heads of KV head hk of sequence b over split j of
-// nsplit_b (tokens [t_begin, t_end)), ending with this split's share of the
-// log-sum-exp merge. Called by every thread of the workgroup. seq_row is
-// seq_start[b] for the contiguous layout (unused when paged); the callers
-// load it together with ctx_lens[b], so the two loads cost one round trip
-// before the first tile is requested.
+// Attention of the G query heads of KV head hk of sequence b over one split
+// (tokens [t_begin, t_end), t_begin a multiple of 32), ending with this
+// split's share of the log-sum-exp merge. Called by every thread of the
+// workgroup. seq_row is seq_start[b] for the contiguous layout (unused when
+// paged); the callers load it together with ctx_lens[b], so the two loads
+// cost one round trip before the first tile is requested.
 //
 // With next_item set (work-queue form), thread 0 takes the workgroup's next
 // item from the queue once the token loop is done: issued earlier, the queue
 // atomic would sit ahead of the tile loads in the in-order memory counter.
-template <int D, Layout LAYOUT, bool FP8>
-__device__ void attend_split(const AttnParams& p, SplitSmem<D, LAYOUT>& sm, int b, int hk, int j, int nsplit_b,
-                             int t_begin, int t_end, int L, int64_t seq_row, int* next_item) {
+template <int D, Layout LAYOUT, bool FP8, typename Parts>
+__device__ void attend_split(const AttnParams& p, WaveState<D>& ws, int b, int hk, const Parts& parts, int t_begin,
+                             int t_end, int L, int64_t seq_row, int* next_item) {
   using TileT = typename TileOf<D, FP8>::type;
+  using LoaderT = Loader<D, LAYOUT, FP8>;
   constexpr int KB = D / 32;
   constexpr int NT = D / 16;
   const int lane = threadIdx.x & 63;
@@ -408,32 +411,31 @@ __device__ void attend_split(const AttnParams& p, SplitSmem<D, LAYOUT>& sm, int 
   const int c = lane & 15, g = lane >> 4;
   const int G = p.group;
 
-  Loader<D, LAYOUT, FP8> ld;
+  LoaderT ld;
   ld.kbase = p.k + hk * p.stride_head;
   ld.vbase = p.v + hk * p.stride_head;
+  ld.bt_row = nullptr;
   if constexpr (LAYOUT == Layout::kContig) {
     const int64_t seq0 = seq_row * p.stride_token;
     ld.kbase += seq0;
     ld.vbase += seq0;
   } else {
-    // Entries for tokens [t_begin, t_end); never past ceil(L / page_size).
-    ld.page_first = t_begin & ~p.page_mask;
-    const int first = t_begin >> p.page_shift;
-    const int count = ((t_end - 1) >> p.page_shift) - first + 1;
-    const int32_t* row = p.block_table + static_cast<int64_t>(b) * p.max_pages + first;
-    for (int i = threadIdx.x; i < count; i += kThreads) sm.pages[i] = checked_page(row[i], p.num_pages, p.errors);
-    __syncthreads();
+    ld.bt_row = p.block_table + static_cast<int64_t>(b) * p.max_pages;
   }
-  ld.sm_pages = sm.pages;
-  ld.stride_token = p.stride_token;
+  ld.pool = static_cast<uint32_t>(min(p.num_pages, int64_t{1} << 31));
+  ld.errors = p.errors;
+  ld.stride_token = static_cast<uint32_t>(p.stride_token);
   ld.stride_page = p.stride_page;
   ld.page_shift = p.page_shift;
   ld.page_mask = p.page_mask;
   ld.t_end = t_end;
+  ld.lane = lane;
   ld.c = c;
   ld.g = g;
   ld.koff = static_cast<uint32_t>(c * p.stride_token + (FP8 ? (D / 4) * g : 16 * g));
-  ld.voff = static_cast<uint32_t>(4 * g * p.stride_token + (FP8 ? NT : 2 * NT) * c);
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    ld.voff[r] = static_cast<uint32_t>((4 * g + r) * p.stride_token + (FP8 ? NT : 2 * NT) * c);
 
   // Q operand: head c of the group (zero columns past G), slice 32kb + 8g
   // (FP8 caches: (D / 4) g + 8 kb, the slice the lane's K codes cover).
@@ -453,9 +455,7 @@ __device__ void attend_split(const AttnParams& p, SplitSmem<D, LAYOUT>& sm, int 
 #pragma unroll
   for (int n = 0; n < NT; ++n) acc[n] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  const int ntok = t_end - t_begin;
-  const int nfull = ntok >> 5;              // full 32-token tiles
-  const int ntiles = (ntok + 31) >> 5;      // including a partial last tile
+  const int ntiles = (t_end - t_begin + 31) >> 5;
   // Fused append: the wave that owns the tile of token L - 1 stores its rows
   // first (not when the length was clamped: that row is not the new token's).
   if (p.new_k != nullptr && t_end == L && L > 0 && w == (ntiles - 1) % kWaves && p.ctx_lens[b] == L) {
@@ -463,45 +463,36 @@ __device__ void attend_split(const AttnParams& p, SplitSmem<D, LAYOUT>& sm, int 
     if constexpr (LAYOUT == Layout::kContig) {
       row = (seq_row + static_cast<int64_t>(L - 1)) * p.stride_token;
     } else {
-      row = checked_page_row(p, sm.pages[((L - 1) - ld.page_first) >> p.page_shift], L - 1);
+      row = checked_page_row(p, ld.bt_row[(L - 1) >> p.page_shift], L - 1);
     }
     store_new_token(p, b, hk, row, FP8 ? D / 16 : D / 8, lane);
   }
-  int ti = w;
-  if constexpr (LAYOUT != Layout::kPagedFine) {
-    // Full tiles w, w + 4, ...: while one tile is computed the next is in
-    // flight. The prefetch is issued unconditionally (past the last full tile
-    // it re-reads cached K rows of the current one) and pinned ahead of the
-    // compute, so the compiler waits for exactly the older tile's loads.
-    if (ti < nfull) {
-      TileT A, B;
-      ld.load_full(A, t_begin + 32 * ti, false);
-      for (;;) {
-        int nx = ti + kWaves;
-        ld.load_full(B, t_begin + 32 * (nx < nfull ? nx : ti), nx >= nfull);
-        __builtin_amdgcn_sched_barrier(0);
-        compute_loaded<D, FP8>(A, t_begin + 32 * ti, t_end, g, qop, p.scale_log2, m_run, l_run, acc);
-        if (nx >= nfull) break;
-        ti = nx;
-        nx = ti + kWaves;
-        ld.load_full(A, t_begin + 32 * (nx < nfull ? nx : ti), nx >= nfull);
-        __builtin_amdgcn_sched_barrier(0);
-        compute_loaded<D, FP8>(B, t_begin + 32 * ti, t_end, g, qop, p.scale_log2, m_run, l_run, acc);
-        if (nx >= nfull) break;
-        ti = nx;
-      }
-    }
-    ti = nfull;  // the partial tile, if any, belongs to wave nfull % kWaves
-    if (ti < ntiles && (ti % kWaves) == w) {
-      TileT A;
-      ld.load_any(A, t_begin + 32 * ti);
-      compute_loaded<D, FP8>(A, t_begin + 32 * ti, t_end, g, qop, p.scale_log2, m_run, l_run, acc);
-    }
-  } else {
-    for (; ti < ntiles; ti += kWaves) {
-      TileT A;
-      ld.load_any(A, t_begin + 32 * ti);
-      compute_loaded<D, FP8>(A, t_begin + 32 * ti, t_end, g, qop, p.scale_log2, m_run, l_run, acc);
+  // Tiles w, w + 4, ...: while one tile is computed the next is in flight.
+  // The prefetch is issued unconditionally (past the wave's last tile it
+  // re-reads cached K rows of that one) and pinned ahead of the compute, so
+  // the compiler waits for exactly the older tile's loads.
+  if (w < ntiles) {
+    const int last = (ntiles - 1 - w) / kWaves;  // the wave's tiles 0 .. last
+    ld.t_first = t_begin + 32 * w;
+    auto token = [&](int n) { return ld.t_first + 32 * kWaves * n; };
+    TileT A, B;
+    ld.first_entries();
+    ld.load(A, 0, token(0), false);
+    for (int n = 0;;) {
+      int nx = min(n + 1, last);
+      if (n < last) ld.next_entries(nx);
+      ld.load(B, nx, token(nx), n == last);
+      __builtin_amdgcn_sched_barrier(0);
+      compute_loaded<D, FP8>(A, token(n), t_end, g, qop, p.scale_log2, m_run, l_run, acc);
+      if (n == last) break;
+      n = nx;
+      nx = min(n + 1, last);
+      if (n < last) ld.next_entries(nx);
+      ld.load(A, nx, token(nx), n == last);
+      __builtin_amdgcn_sched_barrier(0);
+      compute_loaded<D, FP8>(B, token(n), t_end, g, qop, p.scale_log2, m_run, l_run, acc);
+      if (n == last) break;
+      n = nx;
     }
   }
 
@@ -512,8 +503,8 @@ __device__ void attend_split(const AttnParams& p, SplitSmem<D, LAYOUT>& sm, int 
   l_run += __shfl_xor(l_run, 16);
   l_run += __shfl_xor(l_run, 32);
   if (g == 0 && c < G) {
-    sm.ws.m[w][c] = m_run;
-    sm.ws.l[w][c] = l_run;
+    ws.m[w][c] = m_run;
+    ws.l[w][c] = l_run;
   }
   // A lane's values of one head are NT consecutive head_dim positions, so
   // they go out as 16-byte stores.
@@ -523,12 +514,32 @@ __device__ void attend_split(const AttnParams& p, SplitSmem<D, LAYOUT>& sm, int 
     if (h < G) {
 #pragma unroll
       for (int n = 0; n < NT; n += 4)
-        *reinterpret_cast<float4*>(&sm.ws.o[w][h][NT * c + n]) =
+        *reinterpret_cast<float4*>(&ws.o[w][h][NT * c + n]) =
             make_float4(acc[n][r], acc[n + 1][r], acc[n + 2][r], acc[n + 3][r]);
     }
   }
   __syncthreads();
-  finalize_split<D>(p, sm.ws, b, hk, j, nsplit_b);
+  finalize_split<D>(p, ws, b, hk, parts);
+}
+
+// a / d for a, d < 2^23 and rd = 1 / d to within two units in the last place:
+// the float quotient is off by at most one.
+__device__ inline uint32_t div_small(uint32_t a, uint32_t d, float rd) {
+  const uint32_t q = static_cast<uint32_t>(static_cast<float>(a) * rd);
+  const int r = static_cast<int>(a - q * d);
+  return r < 0 ? q - 1 : (r >= static_cast<int>(d) ? q + 1 : q);
+}
+
+// Tiles of a sequence (an empty one has one, empty, tile).
+__device__ inline int tiles_of(int L) { return L > 0 ? (L + 31) >> 5 : 1; }
+
+// Tiles per range of a call of `total` tiles: an equal share of the ranges,
+// but no less than a piece should have (see decode_mfma_balanced_kernel).
+__device__ inline int range_tiles(const AttnParams& p, int total) {
+  const int share = static_cast<int>(
+      div_small(total + p.ranges - 1, p.ranges, __builtin_amdgcn_rcpf(static_cast<float>(p.ranges))));
+  const float piece = __builtin_ceilf(__builtin_amdgcn_sqrtf(p.split_coef * static_cast<float>(total)));
+  return uniform_i32(max(share, max(2, static_cast<int>(piece))));
 }
 
 // One workgroup per (split, KV head, sequence); splits past a sequence's end
@@ -539,6 +550,11 @@ __device__ void attend_split(const AttnParams& p, SplitSmem<D, LAYOUT>& sm, int 
 // in two allocations took 29.1 instead of 30.3 us (27.8 and 27.9 us with the
 // recommended placement). Grids of more than 2^24 workgroups per sequence
 // keep the direct order (the 32-bit index arithmetic stays exact).
+//
+// A planned call of one sequence comes here with p.ranges set: its balanced
+// ranges are even splits whose size follows from L, and the balanced kernel's
+// prefix sums and search cost 0.9 us (us, 1024-token splits / now, bf16,
+// G = 4, 8 KV heads: 1000 tokens 13.8 / 7.2, 4000 17.1 / 10.0, 6001 17.4 / 11.0).
 template <int D, Layout LAYOUT, bool FP8>
 __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(const AttnParams p) {
   int j = blockIdx.x, hk = blockIdx.y;
@@ -551,11 +567,12 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(const AttnPara
   int L;
   int64_t seq_row;
   load_sequence<LAYOUT>(p, b, L, seq_row);
-  const int nsplit_b = L > 0 ? 1 + (L - 1) / p.chunk : 1;  // even splits (no short last ones)
-  if (j >= nsplit_b) return;
-  const int t0 = j * p.chunk;
-  __shared__ SplitSmem<D, LAYOUT> sm;
-  attend_split<D, LAYOUT, FP8>(p, sm, b, hk, j, nsplit_b, t0, t0 + min(L - t0, p.chunk), L, seq_row, nullptr);
+  const int chunk = p.ranges > 0 ? 32 * range_tiles(p, tiles_of(L)) : p.chunk;
+  const EvenParts parts(p, b, hk, j, L, chunk);
+  if (j >= parts.count) return;
+  const int t0 = j * chunk;
+  __shared__ WaveState<D> ws;
+  attend_split<D, LAYOUT, FP8>(p, ws, b, hk, parts, t0, t0 + min(L - t0, chunk), L, seq_row, nullptr);
 }
 
 // In-place prefix sum by one wave: a[i + 1] (counts of sequences 0..n-1)
@@ -586,37 +603,30 @@ __device__ inline int find_sequence(const int* first, int n, int index) {
   return lo;
 }
 
-// Persistent workgroups that take work items from a queue. The items are
-// the large splits of every sequence, in the order (b, j, hk) so that the
-// heads of one token range are adjacent and sequences follow each other,
-// then the short last splits (SplitGeometry) in the same order. Which
-// workgroup runs an item depends on timing, but every item computes the same
-// values and the merge order is fixed, so results do not. The queue counter
-// and the count of finished workgroups live next to the tickets and return
-// to zero when the last workgroup leaves. Faster XCDs and compute units
-// simply take more items, and ragged batches need no empty workgroups.
+// Persistent workgroups that take work items from a queue: the form for a
+// configured split size with more items than workgroups. The items are the
+// splits of every sequence in the order (b, j, hk), so that the heads of one
+// token range are adjacent and sequences follow each other. Which workgroup
+// runs an item depends on timing, but every item computes the same values
+// and the merge order is fixed, so results do not. The queue counter and the
+// count of finished workgroups live next to the tickets and return to zero
+// when the last workgroup leaves. Faster XCDs and compute units simply take
+// more items, and ragged batches need no empty workgroups.
 template <int D, Layout LAYOUT, bool FP8>
 __global__ __launch_bounds__(kThreads, 2) void decode_mfma_queue_kernel(const AttnParams p, int batch) {
-  __shared__ SplitSmem<D, LAYOUT> sm;
-  __shared__ int sm_first[kMaxQueueBatch + 1];  // prefix sums of large splits per sequence
-  __shared__ int sm_short[kMaxQueueBatch + 1];  // prefix sums of short splits per sequence
+  __shared__ WaveState<D> ws;
+  __shared__ int sm_first[kMaxQueueBatch + 1];  // prefix sums of splits per sequence
   __shared__ int sm_next;
   const int tid = threadIdx.x;
   uint32_t* queue = p.tickets + p.queue_slot;
   uint32_t* finished = queue + 1;
 
-  // Split counts per sequence, then prefix sums (one wave each).
-  for (int b = tid; b < batch; b += kThreads) {
-    const SplitGeometry geo(checked_len(p.ctx_lens[b], p.max_ctx, nullptr), p);  // reported by load_sequence
-    sm_first[b + 1] = geo.big();
-    sm_short[b + 1] = geo.small;
-  }
+  for (int b = tid; b < batch; b += kThreads)  // a length out of bounds is reported by load_sequence
+    sm_first[b + 1] = EvenParts::splits(checked_len(p.ctx_lens[b], p.max_ctx, nullptr), p.chunk);
   __syncthreads();
   if (tid < 64) wave_prefix_sum(sm_first, batch, tid);
-  else if (tid < 128) wave_prefix_sum(sm_short, batch, tid - 64);
   __syncthreads();
-  const int total_big = sm_first[batch] * p.num_kv_heads;
-  const int total = total_big + sm_short[batch] * p.num_kv_heads;
+  const int total = sm_first[batch] * p.num_kv_heads;
   // Item blockIdx.x first; later items come from the queue, which hands out
   // gridDim.x, gridDim.x + 1, ... Without more items than workgroups the
   // queue is never touched.
@@ -624,19 +634,16 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_queue_kernel(const At
 
   int item = blockIdx.x;
   while (item < total) {
-    const bool is_big = item < total_big;
-    const int index = (is_big ? item : item - total_big) / p.num_kv_heads;
-    const int hk = (is_big ? item : item - total_big) - index * p.num_kv_heads;
-    const int b = find_sequence(is_big ? sm_first : sm_short, batch, index);
-    const int big_b = sm_first[b + 1] - sm_first[b];
-    const int j = is_big ? index - sm_first[b] : big_b + index - sm_short[b];
+    const int index = item / p.num_kv_heads;
+    const int hk = item - index * p.num_kv_heads;
+    const int b = find_sequence(sm_first, batch, index);
+    const int j = index - sm_first[b];
     int L;
     int64_t seq_row;
     load_sequence<LAYOUT>(p, b, L, seq_row);
-    const SplitGeometry geo(L, p);
-    int t0, t1;
-    geo.range(j, L, p, t0, t1);
-    attend_split<D, LAYOUT, FP8>(p, sm, b, hk, j, geo.nsplit, t0, t1, L, seq_row, queued ? &sm_next : nullptr);
+    const int t0 = j * p.chunk;
+    attend_split<D, LAYOUT, FP8>(p, ws, b, hk, EvenParts(p, b, hk, j, L, p.chunk), t0, t0 + min(L - t0, p.chunk), L, seq_row,
+                                 queued ? &sm_next : nullptr);
     __syncthreads();
     item = queued ? sm_next : total;
     __syncthreads();
@@ -644,6 +651,91 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_queue_kernel(const At
   if (queued && tid == 0 && atomicAdd(finished, 1u) == gridDim.x - 1) {
     atomicExch(queue, 0u);
     atomicExch(finished, 0u);
+  }
+}
+
+// The balanced form, for planned splits: the 32-token tiles of all sequences,
+// one after the other, are cut into p.ranges equal ranges, and workgroup
+// (hk, r) attends over range r of KV head hk, in one piece per sequence that
+// the range touches. A sequence inside one range is written directly; the
+// pieces of one that several ranges share are merged by the last to finish.
+//
+// HBM bandwidth bounds it, and one workgroup per CU with one long equal piece
+// of work reads faster than more, shorter items: fewer times does a workgroup
+// stop reading to merge its waves and publish (about 10 us under load), and
+// no last round of items runs on a part of the chip. Measured (us, work queue
+// of 1024- to 4096-token splits / balanced): 8 x 131072 tokens, G = 8, 4 GiB
+// in 64-token pages 661 / 628 (6.8 TB/s); 16 x 4K-64K packed 380 / 357; 64 x
+// 2K-16K in 16-token pages 382 / 363.
+// With the heads of a range in adjacent workgroups, its rows are read side by
+// side, and with 8 KV heads a head stays on one XCD.
+//
+// Short calls are bounded by latency instead: a longer range costs time per
+// token on its one CU, a shorter one more partial results to merge. With a
+// per token and m per split, a length n splits best into pieces of
+// sqrt(m n / a) tokens; p.split_coef holds m / (32 a batch), and no range is
+// shorter than that length for the mean sequence of the call (nor than 64
+// tokens).
+template <int D, Layout LAYOUT, bool FP8>
+__global__ __launch_bounds__(kThreads, 2) void decode_mfma_balanced_kernel(const AttnParams p, int batch) {
+  __shared__ WaveState<D> ws;
+  __shared__ int sm_first[kMaxQueueBatch + 1];  // batches over 64: prefix sums of tiles per sequence
+  const int hk = blockIdx.x, r = blockIdx.y;
+  const int lane = threadIdx.x & 63;
+  // Tiles per sequence (an empty one has one, empty, tile) as prefix sums:
+  // up to 64 sequences in the lanes of every wave, else in LDS.
+  const bool in_lanes = batch <= 64;
+  int len = 0, incl = 0, total;
+  int64_t row = 0;  // seq_start, requested together with the length
+  if (in_lanes) {
+    if (lane < batch) {
+      len = p.ctx_lens[lane];
+      if constexpr (LAYOUT == Layout::kContig) row = p.seq_start[lane];
+      len = checked_len(len, p.max_ctx, p.errors);
+      incl = tiles_of(len);
+    }
+    for (int o = 1; o < batch; o <<= 1) {
+      const int u = __shfl_up(incl, o);
+      if (lane >= o) incl += u;
+    }
+    total = __builtin_amdgcn_readlane(incl, batch - 1);
+  } else {
+    for (int b = threadIdx.x; b < batch; b += kThreads)
+      sm_first[b + 1] = tiles_of(checked_len(p.ctx_lens[b], p.max_ctx, p.errors));
+    __syncthreads();
+    if (threadIdx.x < 64) wave_prefix_sum(sm_first, batch, lane);
+    __syncthreads();
+    total = uniform_i32(sm_first[batch]);
+  }
+  const int per = range_tiles(p, total);
+  const float rper = __builtin_amdgcn_rcpf(static_cast<float>(per));
+  int cur = r * per;
+  if (cur >= total) return;
+  const int stop = min(cur + per, total);
+  int b = in_lanes ? __builtin_ctzll(__builtin_amdgcn_ballot_w64(lane < batch && incl > cur))
+                   : uniform_i32(find_sequence(sm_first, batch, cur));
+  for (;;) {
+    const int first = in_lanes ? (b > 0 ? __builtin_amdgcn_readlane(incl, b - 1) : 0) : uniform_i32(sm_first[b]);
+    const int end = in_lanes ? __builtin_amdgcn_readlane(incl, b) : uniform_i32(sm_first[b + 1]);
+    int L;
+    int64_t seq_row;
+    if (in_lanes) {
+      L = __builtin_amdgcn_readlane(len, b);
+      const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(row), b);
+      const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(row >> 32), b);
+      seq_row = static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
+    } else {
+      load_sequence<LAYOUT>(p, b, L, seq_row);
+    }
+    const int piece_end = min(stop, end);
+    const int r0 = uniform_i32(static_cast<int>(div_small(first, per, rper)));
+    const int r1 = uniform_i32(static_cast<int>(div_small(end - 1, per, rper)));
+    attend_split<D, LAYOUT, FP8>(p, ws, b, hk, RangeParts(p, hk, r, r0, r1), 32 * (cur - first),
+                                 min(L, 32 * (piece_end - first)), L, seq_row, nullptr);
+    cur = piece_end;
+    if (cur >= stop) return;
+    ++b;
+    __syncthreads();  // the wave states are rewritten
   }
 }
 
@@ -665,6 +757,13 @@ QueueKernelFn pick_queue_layout(bool paged, int page_size) {
                          : decode_mfma_queue_kernel<D, Layout::kPagedFine, FP8>;
 }
 
+template <int D, bool FP8>
+QueueKernelFn pick_balanced_layout(bool paged, int page_size) {
+  if (!paged) return decode_mfma_balanced_kernel<D, Layout::kContig, FP8>;
+  return page_size >= 16 ? decode_mfma_balanced_kernel<D, Layout::kPaged, FP8>
+                         : decode_mfma_balanced_kernel<D, Layout::kPagedFine, FP8>;
+}
+
 KernelFn select_mfma_kernel(int head_dim, bool paged, int page_size, bool fp8) {
   if (head_dim == 128) return fp8 ? pick_layout<128, true>(paged, page_size) : pick_layout<128, false>(paged, page_size);
   if (head_dim == 64) return fp8 ? pick_layout<64, true>(paged, page_size) : pick_layout<64, false>(paged, page_size);
@@ -679,8 +778,14 @@ QueueKernelFn select_mfma_queue_kernel(int head_dim, bool paged, int page_size, 
   return nullptr;
 }
 
-int mfma_max_queue_batch() { return kMaxQueueBatch; }
+QueueKernelFn select_mfma_balanced_kernel(int head_dim, bool paged, int page_size, bool fp8) {
+  if (head_dim == 128)
+    return fp8 ? pick_balanced_layout<128, true>(paged, page_size) : pick_balanced_layout<128, false>(paged, page_size);
+  if (head_dim == 64)
+    return fp8 ? pick_balanced_layout<64, true>(paged, page_size) : pick_balanced_layout<64, false>(paged, page_size);
+  return nullptr;
+}
 
-int mfma_max_split_pages() { return kMaxSplitPages; }
+int mfma_max_queue_batch() { return kMaxQueueBatch; }
 
 }  // namespace comem

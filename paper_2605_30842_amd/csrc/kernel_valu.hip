@@ -49,8 +49,8 @@ __global__ __launch_bounds__(kThreads) void decode_valu_kernel(const AttnParams 
   constexpr int TT = RPL * U;     // tokens per tile
   const int j = blockIdx.x, hk = blockIdx.y, b = blockIdx.z;
   const int L = checked_len(p.ctx_lens[b], p.max_ctx, p.errors);
-  const int nsplit_b = L > 0 ? 1 + (L - 1) / p.chunk : 1;
-  if (j >= nsplit_b) return;
+  const EvenParts parts(p, b, hk, j, L, p.chunk);
+  if (j >= parts.count) return;
   const int t_begin = j * p.chunk;
   const int t_end = t_begin + min(L - t_begin, p.chunk);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -176,7 +176,7 @@ __global__ __launch_bounds__(kThreads) void decode_valu_kernel(const AttnParams 
     }
   }
   __syncthreads();
-  finalize_split<D>(p, ws, b, hk, j, nsplit_b);
+  finalize_split<D>(p, ws, b, hk, parts);
 }
 
 template <typename T, int D, bool PAGED>

@@ -17,3 +17,28 @@ def test_spread_tickets_fit_wherever_dense_ones_did(max_batch):
         assert st == (B.ERR_NO_DEVICE if dense <= 65536 else B.ERR_SCRATCH_LIMIT)
     finally:
         B.comem_decode_attn_destroy(p)
+
+
+@pytest.mark.parametrize("batch,L,chunk", [
+    (1, 2048, 128),   # latency-bound: pieces worth their merge
+    (1, 8192, 256),   # one split per compute unit
+    (6, 4096, 832),   # 5 splits for each of 48 (sequence, head) pairs
+    (4, 16384, 1024),  # never above 1024 while some unit is free
+    (32, 3000, 3008),  # the pairs fill the chip: no split
+])
+def test_short_calls_plan_one_split_per_compute_unit(batch, L, chunk):
+    p, ws = B.comem_decode_attn_init(_cfg(max_batch=batch, max_ctx_len=L), B.NO_DEVICE)
+    try:
+        assert B.comem_decode_attn_plan_splits(p, batch, L, ws) == (chunk, -(-L // chunk))
+    finally:
+        B.comem_decode_attn_destroy(p)
+
+
+def test_a_small_workspace_still_gets_every_call():
+    """A workspace below what short splits need gets longer ones, down to one that needs none."""
+    p, ws = B.comem_decode_attn_init(_cfg(max_batch=1, max_ctx_len=8192), B.NO_DEVICE)
+    try:
+        sizes = [B.comem_decode_attn_plan_splits(p, 1, 8192, n)[0] for n in (ws, 600000, 300000, 40000, 0)]
+        assert sizes == sorted(sizes) and sizes[0] == 256 and sizes[-1] >= 8192
+    finally:
+        B.comem_decode_attn_destroy(p)
