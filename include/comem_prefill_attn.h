@@ -26,7 +26,9 @@
  * whose dtype is COMEM_BF16; its heads, head_dim (64 or 128), scale,
  * max_batch and max_ctx_len apply, its chunk_tokens and variant do not. They
  * need no workspace, enqueue one kernel on the given stream and return; they
- * never allocate, synchronise, or read device memory from the host.
+ * never allocate, synchronise, or read device memory from the host. The
+ * split forms below take a workspace besides and are faster where a few new
+ * tokens attend over a long prefix.
  *
  * Ownership: the caller owns every device buffer. Errors: as for the decode
  * calls, every argument is checked on the host before any HIP call and a bad
@@ -79,6 +81,34 @@ comem_status comem_prefill_attn_paged(const comem_decode_attn_plan* plan, const 
                                       const int32_t* block_table, int32_t max_pages_per_seq,
                                       const int32_t* ctx_lens, int32_t batch, int64_t max_ctx_len, float* out,
                                       float* lse, void* hip_stream);
+
+/* The same calls with a workspace. A query block's keys are then shared by
+ * several workgroups where that is faster (a few new tokens over a long
+ * prefix fill only a part of the GPU otherwise), and a second kernel on the
+ * same stream merges their partial results in a fixed order.
+ * comem_prefill_attn_workspace stores in *workspace_bytes_out the bytes that
+ * a call with these bounds can use (0: it would not split; both forms then do
+ * the same). The split calls take a workspace of any size: with less, or
+ * NULL, they split less or not at all. The workspace is device memory,
+ * 256-byte aligned, needs no initialisation, holds nothing between calls and
+ * must not be used by two calls that can run at the same time. Other
+ * arguments, checks and results as above. */
+comem_status comem_prefill_attn_workspace(const comem_decode_attn_plan* plan, int32_t batch, int32_t max_q_len,
+                                          int64_t max_ctx_len, size_t* workspace_bytes_out);
+
+comem_status comem_prefill_attn_split(const comem_decode_attn_plan* plan, const void* q, const int64_t* q_start,
+                                      const int32_t* q_lens, int32_t max_q_len, const void* k, const void* v,
+                                      int64_t stride_token, int64_t stride_head, const int64_t* seq_start,
+                                      const int32_t* ctx_lens, int32_t batch, int64_t max_ctx_len, float* out,
+                                      float* lse, void* workspace, size_t workspace_bytes, void* hip_stream);
+
+comem_status comem_prefill_attn_split_paged(const comem_decode_attn_plan* plan, const void* q, const int64_t* q_start,
+                                            const int32_t* q_lens, int32_t max_q_len, const void* k_pages,
+                                            const void* v_pages, int64_t stride_page, int64_t stride_token,
+                                            int64_t stride_head, int32_t page_size, int64_t num_pages,
+                                            const int32_t* block_table, int32_t max_pages_per_seq,
+                                            const int32_t* ctx_lens, int32_t batch, int64_t max_ctx_len, float* out,
+                                            float* lse, void* workspace, size_t workspace_bytes, void* hip_stream);
 
 #ifdef __cplusplus
 }

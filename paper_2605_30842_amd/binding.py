@@ -31,7 +31,8 @@ EXPORTED = (
     "comem_decode_attn_plan_splits", "comem_decode_attn", "comem_decode_attn_paged",
     "comem_kv_append", "comem_kv_append_paged", "comem_append_decode_attn", "comem_append_decode_attn_paged",
     "comem_prefill_attn", "comem_prefill_attn_paged", "comem_decode_attn_device_errors",
-    "comem_decode_attn_noalloc",
+    "comem_decode_attn_noalloc", "comem_prefill_attn_workspace", "comem_prefill_attn_split",
+    "comem_prefill_attn_split_paged",
 )
 NOALLOC_SCRATCH_BYTES = 32 << 20  # COMEM_NOALLOC_SCRATCH_BYTES
 FLAG_DEBUG_CHECKS = 1
@@ -145,6 +146,14 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.comem_prefill_attn_paged.argtypes = [vp, vp, vp, vp, i32, vp, vp, i64, i64, i64, i32, i64, vp, i32, vp,
                                              i32, i64, vp, vp, vp]
     lib.comem_prefill_attn_paged.restype = ctypes.c_int
+    lib.comem_prefill_attn_workspace.argtypes = [vp, i32, i32, i64, ctypes.POINTER(sz)]
+    lib.comem_prefill_attn_workspace.restype = ctypes.c_int
+    lib.comem_prefill_attn_split.argtypes = [vp, vp, vp, vp, i32, vp, vp, i64, i64, vp, vp, i32, i64, vp, vp, vp, sz,
+                                             vp]
+    lib.comem_prefill_attn_split.restype = ctypes.c_int
+    lib.comem_prefill_attn_split_paged.argtypes = [vp, vp, vp, vp, i32, vp, vp, i64, i64, i64, i32, i64, vp, i32, vp,
+                                                   i32, i64, vp, vp, vp, sz, vp]
+    lib.comem_prefill_attn_split_paged.restype = ctypes.c_int
     _lib = lib
     return lib
 
@@ -306,6 +315,30 @@ def comem_prefill_attn_paged(plan, q, q_start, q_lens, max_q_len, k_pages, v_pag
            "comem_prefill_attn_paged")
 
 
+def comem_prefill_attn_workspace(plan, batch, max_q_len, max_ctx_len) -> int:
+    nbytes = ctypes.c_size_t()
+    _check(load_library().comem_prefill_attn_workspace(plan, batch, max_q_len, max_ctx_len, ctypes.byref(nbytes)),
+           "comem_prefill_attn_workspace")
+    return nbytes.value
+
+
+def comem_prefill_attn_split(plan, q, q_start, q_lens, max_q_len, k, v, stride_token, stride_head, seq_start,
+                             ctx_lens, batch, max_ctx_len, out, lse, workspace, workspace_bytes, stream) -> None:
+    _check(load_library().comem_prefill_attn_split(plan, q, q_start, q_lens, max_q_len, k, v, stride_token,
+                                                   stride_head, seq_start, ctx_lens, batch, max_ctx_len, out, lse,
+                                                   workspace, workspace_bytes, stream), "comem_prefill_attn_split")
+
+
+def comem_prefill_attn_split_paged(plan, q, q_start, q_lens, max_q_len, k_pages, v_pages, stride_page, stride_token,
+                                   stride_head, page_size, num_pages, block_table, max_pages_per_seq, ctx_lens,
+                                   batch, max_ctx_len, out, lse, workspace, workspace_bytes, stream) -> None:
+    _check(load_library().comem_prefill_attn_split_paged(plan, q, q_start, q_lens, max_q_len, k_pages, v_pages,
+                                                         stride_page, stride_token, stride_head, page_size, num_pages,
+                                                         block_table, max_pages_per_seq, ctx_lens, batch, max_ctx_len,
+                                                         out, lse, workspace, workspace_bytes, stream),
+           "comem_prefill_attn_split_paged")
+
+
 def _cost_call(name, *args) -> float:
     out = ctypes.c_double()
     _check(getattr(load_library(), name)(*args, ctypes.byref(out)), name)
@@ -400,6 +433,10 @@ def kv_cache_pair(shape, dtype, device):
     if (v.data_ptr() - k.data_ptr()) % V_BASE_OFFSET_MODULUS != V_BASE_OFFSET_BYTES:
         raise RuntimeError("K/V placement not reached (allocation misaligned)")
     return k, v
+
+
+# Shorter contexts hold fewer than two splits' worth of keys: not worth asking for a prefill workspace.
+PREFILL_SPLIT_MIN_CTX = 1024
 
 
 class DecodeAttention:
@@ -603,6 +640,22 @@ class DecodeAttention:
             out = torch.empty(q.shape, dtype=torch.float32, device=q.device)
         return out, lse
 
+    def _prefill_workspace(self, batch, max_q_len, max_ctx_len, stream):
+        """Scratch of one prefill call, or None when the library would not use any. It comes from torch's allocator
+        on the call's stream and goes back to it when the call has been enqueued: no two calls share it, whatever
+        their streams and threads, and later work on the stream may reuse it."""
+        import torch
+
+        if max_ctx_len < PREFILL_SPLIT_MIN_CTX:
+            return None
+        nbytes = comem_prefill_attn_workspace(self.plan, batch, max_q_len, max_ctx_len)
+        if nbytes == 0:
+            return None
+        if stream is None:
+            return torch.empty(nbytes, dtype=torch.uint8, device=self._torch_device)
+        with torch.cuda.stream(stream):
+            return torch.empty(nbytes, dtype=torch.uint8, device=self._torch_device)
+
     def prefill(self, q, q_start, q_lens, max_q_len: int, k, v, seq_start, ctx_lens, max_ctx_len: int, out=None,
                 lse=None, stream=None):
         """Prefill attention of the packed new tokens q [total, Hq, D] over a contiguous cache."""
@@ -610,10 +663,14 @@ class DecodeAttention:
         self._check_cache(k, v, paged=False)
         self._check_lengths(ctx_lens, ctx_lens.shape[0], seq_start=seq_start)
         out, lse = self._prefill_outputs(q, out, lse)
-        comem_prefill_attn(self.plan, q.data_ptr(), q_start.data_ptr(), q_lens.data_ptr(), int(max_q_len),
-                           k.data_ptr(), v.data_ptr(), k.stride(0), k.stride(1), seq_start.data_ptr(),
-                           ctx_lens.data_ptr(), ctx_lens.shape[0], int(max_ctx_len), out.data_ptr(),
-                           None if lse is None else lse.data_ptr(), self._stream(stream))
+        args = (self.plan, q.data_ptr(), q_start.data_ptr(), q_lens.data_ptr(), int(max_q_len), k.data_ptr(),
+                v.data_ptr(), k.stride(0), k.stride(1), seq_start.data_ptr(), ctx_lens.data_ptr(), ctx_lens.shape[0],
+                int(max_ctx_len), out.data_ptr(), None if lse is None else lse.data_ptr())
+        ws = self._prefill_workspace(ctx_lens.shape[0], int(max_q_len), int(max_ctx_len), stream)
+        if ws is None:
+            comem_prefill_attn(*args, self._stream(stream))
+        else:
+            comem_prefill_attn_split(*args, ws.data_ptr(), ws.numel(), self._stream(stream))
         return out, lse
 
     def prefill_paged(self, q, q_start, q_lens, max_q_len: int, k_pages, v_pages, block_table, ctx_lens,
@@ -622,9 +679,13 @@ class DecodeAttention:
         self._check_cache(k_pages, v_pages, paged=True)
         self._check_lengths(ctx_lens, ctx_lens.shape[0], block_table=block_table)
         out, lse = self._prefill_outputs(q, out, lse)
-        comem_prefill_attn_paged(self.plan, q.data_ptr(), q_start.data_ptr(), q_lens.data_ptr(), int(max_q_len),
-                                 k_pages.data_ptr(), v_pages.data_ptr(), k_pages.stride(0), k_pages.stride(1),
-                                 k_pages.stride(2), k_pages.shape[1], k_pages.shape[0], block_table.data_ptr(),
-                                 block_table.shape[1], ctx_lens.data_ptr(), ctx_lens.shape[0], int(max_ctx_len),
-                                 out.data_ptr(), None if lse is None else lse.data_ptr(), self._stream(stream))
+        args = (self.plan, q.data_ptr(), q_start.data_ptr(), q_lens.data_ptr(), int(max_q_len), k_pages.data_ptr(),
+                v_pages.data_ptr(), k_pages.stride(0), k_pages.stride(1), k_pages.stride(2), k_pages.shape[1],
+                k_pages.shape[0], block_table.data_ptr(), block_table.shape[1], ctx_lens.data_ptr(),
+                ctx_lens.shape[0], int(max_ctx_len), out.data_ptr(), None if lse is None else lse.data_ptr())
+        ws = self._prefill_workspace(ctx_lens.shape[0], int(max_q_len), int(max_ctx_len), stream)
+        if ws is None:
+            comem_prefill_attn_paged(*args, self._stream(stream))
+        else:
+            comem_prefill_attn_split_paged(*args, ws.data_ptr(), ws.numel(), self._stream(stream))
         return out, lse

@@ -435,8 +435,14 @@ __device__ inline void stage_barrier() {
   asm volatile("" ::: "memory");
 }
 
-// Grid: (query blocks, KV heads, sequences); the kernel maps the workgroup
-// id to a work item itself (see the top of the kernel).
+// First row of a split's partial results.
+__device__ inline int64_t prefill_part(const PrefillParams& p, int b, int hk, int q, int split) {
+  const int64_t item = (static_cast<int64_t>(b) * (p.num_q_heads / p.group) + hk) * p.blocks + q;
+  return (item * p.splits + split) * kPrefillRows;
+}
+
+// Grid: (query blocks times splits, KV heads, sequences); the kernel maps the
+// workgroup id to a work item itself (see the top of the kernel).
 constexpr int kXcds = 8;  // XCDs of the GPU; workgroups are dealt to them round robin
 
 // One workgroup of 8 waves per block of 128 rows: waves 4..7 take the same
@@ -464,7 +470,7 @@ __global__ __launch_bounds__(kPrefillThreads, 1) void prefill_mfma_kernel(const 
     const int lin = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
     const int x = lin % kXcds, k = lin / kXcds;
     const int r = k / gridDim.x;
-    q = k - r * static_cast<int>(gridDim.x);
+    q = k - r * static_cast<int>(gridDim.x);  // (split, block) of the pair
     const int hbp = x + kXcds * r;
     b = hbp / gridDim.y;
     hk = hbp - b * static_cast<int>(gridDim.y);
@@ -473,6 +479,10 @@ __global__ __launch_bounds__(kPrefillThreads, 1) void prefill_mfma_kernel(const 
     hk = blockIdx.y;
     q = blockIdx.x;
   }
+  // The splits of a block's keys: the blocks of one split run side by side,
+  // so they share its K/V tiles in L2 like those of an unsplit call.
+  const int split = p.splits > 1 ? q / p.blocks : 0;
+  q -= split * p.blocks;
   const int TB = p.tokens_per_block;
 
   int L = p.ctx_lens[b];
@@ -488,7 +498,11 @@ __global__ __launch_bounds__(kPrefillThreads, 1) void prefill_mfma_kernel(const 
   const int i0 = (nblk - 1 - q) * TB;
   const int prefix = L - M;
   const int kend = prefix + min(M, i0 + TB);  // keys any row of this block sees
-  const int ntiles = (kend + kPrefillTileKeys - 1) / kPrefillTileKeys;
+  const int all_tiles = (kend + kPrefillTileKeys - 1) / kPrefillTileKeys;
+  // This split's tiles: first_tile .. first_tile + ntiles - 1 (an equal share).
+  const int share = p.splits > 1 ? (all_tiles + p.splits - 1) / p.splits : all_tiles;
+  const int first_tile = split * share;
+  const int ntiles = min(share, max(all_tiles - first_tile, 0));
   const int nfree = (prefix + i0 + 1) / kPrefillTileKeys;  // tiles visible to every row
 
   const int lane = threadIdx.x & 63;
@@ -544,8 +558,8 @@ __global__ __launch_bounds__(kPrefillThreads, 1) void prefill_mfma_kernel(const 
   __shared__ LdsTile<D> ks0[2], ks1[2], vs0[2], vs1[2];
   using Pages = typename TileLoader<D, LAYOUT>::Pages;
   const int steps = (ntiles + 1) / 2;
-  const int t_first = kh * steps;
-  const int t_count = max(0, min(steps, ntiles - t_first));
+  const int t_first = first_tile + kh * steps;
+  const int t_count = max(0, min(steps, ntiles - kh * steps));
   constexpr int TK = kPrefillTileKeys;
   LdsTile<D>& k0 = ks0[kh];
   LdsTile<D>& k1 = ks1[kh];
@@ -654,8 +668,10 @@ __global__ __launch_bounds__(kPrefillThreads, 1) void prefill_mfma_kernel(const 
     if (kh == 0 && (w >> 1) == pass) {
       const float m1 = ml[w * 64 + lane];
       const float l1 = ml[256 + w * 64 + lane];
-      const float mn = fmaxf(m_run, m1);  // finite: half 0 holds key 0, visible to every row
-      const float a0 = fast_exp2((m_run - mn) * p.scale_log2);
+      // Of an unsplit call half 0 holds key 0, which every row sees; a later
+      // split may hold no key that the row sees at all.
+      const float mn = fmaxf(m_run, m1);
+      const float a0 = m_run == -INFINITY ? 0.f : fast_exp2((m_run - mn) * p.scale_log2);
       const float a1 = m1 == -INFINITY ? 0.f : fast_exp2((m1 - mn) * p.scale_log2);
 #pragma unroll
       for (int n = 0; n < NT; ++n)
@@ -674,9 +690,17 @@ __global__ __launch_bounds__(kPrefillThreads, 1) void prefill_mfma_kernel(const 
   }
   if (kh == 1) return;
   if (i >= M) return;
-  const float inv = 1.f / l_run;
+  float inv = 1.f / l_run;
   const int64_t orow = (qs + i) * p.num_q_heads + qh;
   float* o = p.out + orow * D;
+  if (p.splits > 1) {
+    // Partial result: normalised over the split's keys, with its log-sum-exp
+    // in log2 units (0 and -inf if the row sees none of them).
+    const int64_t part = prefill_part(p, b, hk, q, split) + row;
+    o = p.o_part + part * D;
+    if (!(l_run > 0.f)) inv = 0.f;
+    if (h == 0) p.lse_part[part] = l_run > 0.f ? m_run * p.scale_log2 + log2f(l_run) : -INFINITY;
+  }
   // acc[n] register r holds head_dim 32 n + 8 (r / 4) + 4 h + r % 4.
 #pragma unroll
   for (int n = 0; n < NT; ++n)
@@ -685,7 +709,70 @@ __global__ __launch_bounds__(kPrefillThreads, 1) void prefill_mfma_kernel(const 
       *reinterpret_cast<float4*>(o + 32 * n + 8 * r4 + 4 * h) =
           make_float4(acc[n][4 * r4] * inv, acc[n][4 * r4 + 1] * inv, acc[n][4 * r4 + 2] * inv,
                       acc[n][4 * r4 + 3] * inv);
-  if (h == 0 && p.lse != nullptr) p.lse[orow] = (m_run * p.scale_log2 + log2f(l_run)) * kLn2;
+  if (h == 0 && p.lse != nullptr && p.splits == 1) p.lse[orow] = (m_run * p.scale_log2 + log2f(l_run)) * kLn2;
+}
+
+// Merge of a split call's partial results. A lane takes 4 head_dim entries
+// of one row and visits the splits in order, kBatch at a time with their
+// loads in flight together: log-weights first (the row's largest, then each
+// split's weight), then the weighted sum. Bandwidth of the partials bounds
+// it: they were written just before and come from the Infinity Cache.
+template <int D>
+__global__ __launch_bounds__(kPrefillMergeThreads) void prefill_merge_kernel(const PrefillParams p) {
+  constexpr int kBatch = 8;
+  constexpr int kSlots = kPrefillMergeRows * D / 4;
+  constexpr int kGroups = kPrefillRows / kPrefillMergeRows;
+  const int q = blockIdx.x / kGroups, hk = blockIdx.y, b = blockIdx.z;
+  const int row0 = (blockIdx.x % kGroups) * kPrefillMergeRows;
+  const int TB = p.tokens_per_block;
+  const int L = min(max(p.ctx_lens[b], 0), p.max_ctx);
+  const int M = min(max(p.q_lens[b], 0), min(L, p.max_q));
+  const int nblk = (M + TB - 1) / TB;
+  if (q >= nblk) return;
+  const int i0 = (nblk - 1 - q) * TB;
+  const int64_t qs = p.q_start[b];
+  const int64_t part0 = prefill_part(p, b, hk, q, 0);
+  for (int slot = threadIdx.x; slot < kSlots; slot += kPrefillMergeThreads) {
+    const int row = row0 + slot / (D / 4);
+    const int d0 = 4 * (slot % (D / 4));
+    const int i = i0 + row % TB;
+    if (i >= M) continue;
+    const float* lp = p.lse_part + part0 + row;
+    const float* op = p.o_part + (part0 + row) * D + d0;
+    float m = -INFINITY, wsum = 0.f;
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int s0 = 0; s0 < p.splits; s0 += kBatch) {
+      float l2[kBatch];
+      float4 o[kBatch];
+#pragma unroll
+      for (int k = 0; k < kBatch; ++k) {
+        const int s = min(s0 + k, p.splits - 1);  // past the last split: re-read it, weight 0
+        l2[k] = lp[s * kPrefillRows];
+        o[k] = *reinterpret_cast<const float4*>(op + static_cast<int64_t>(s) * (kPrefillRows * D));
+      }
+      float mn = m;
+#pragma unroll
+      for (int k = 0; k < kBatch; ++k) {
+        if (s0 + k >= p.splits) l2[k] = -INFINITY;
+        mn = fmaxf(mn, l2[k]);
+      }
+      const float a = m == -INFINITY ? 0.f : fast_exp2(m - mn);  // the first split holds key 0: mn is finite
+      acc = make_float4(acc.x * a, acc.y * a, acc.z * a, acc.w * a);
+      wsum *= a;
+#pragma unroll
+      for (int k = 0; k < kBatch; ++k) {
+        const float w = fast_exp2(l2[k] - mn);
+        wsum += w;
+        acc = make_float4(fmaf(w, o[k].x, acc.x), fmaf(w, o[k].y, acc.y), fmaf(w, o[k].z, acc.z),
+                          fmaf(w, o[k].w, acc.w));
+      }
+      m = mn;
+    }
+    const float inv = 1.f / wsum;
+    const int64_t orow = (qs + i) * p.num_q_heads + hk * p.group + row / TB;
+    *reinterpret_cast<float4*>(p.out + orow * D + d0) = make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
+    if (d0 == 0 && p.lse != nullptr) p.lse[orow] = (m + log2f(wsum)) * kLn2;
+  }
 }
 
 // Every form the host may launch, instantiated explicitly (clang emitted the
@@ -698,17 +785,24 @@ COMEM_PREFILL_FORMS(64, kContig)
 COMEM_PREFILL_FORMS(64, kPaged)
 COMEM_PREFILL_FORMS(64, kPagedFine)
 #undef COMEM_PREFILL_FORMS
+template __global__ void prefill_merge_kernel<128>(const PrefillParams);
+template __global__ void prefill_merge_kernel<64>(const PrefillParams);
 
 }  // namespace
 
 template <int D>
 PrefillKernelFn prefill_by_layout(int page_size) {
   // page_size 0: contiguous cache. A paged cache takes the per-group path when
-  // a wave's 16-row group of a tile fits in a page.
+  // a wave's 16-row group of a tile fits in a page (it starts at a multiple of
+  // 16 for either head_dim).
   PrefillKernelFn fn = prefill_mfma_kernel<D, PLayout::kPagedFine>;
   if (page_size == 0) fn = prefill_mfma_kernel<D, PLayout::kContig>;
-  else if (page_size >= 2048 / D) fn = prefill_mfma_kernel<D, PLayout::kPaged>;
+  else if (page_size >= 16) fn = prefill_mfma_kernel<D, PLayout::kPaged>;
   return fn;
+}
+
+PrefillKernelFn select_prefill_merge_kernel(int head_dim) {
+  return head_dim == 128 ? prefill_merge_kernel<128> : (head_dim == 64 ? prefill_merge_kernel<64> : nullptr);
 }
 
 PrefillKernelFn select_prefill_kernel(int head_dim, int page_size) {

@@ -35,10 +35,20 @@ struct PrefillParams {
   int32_t max_ctx;             // ctx_lens[b] is clamped to [0, max_ctx]
   int32_t max_q;               // q_lens[b] is clamped to [0, min(L_b, max_q)]
   int64_t num_pages;           // paged layout: entries outside [0, num_pages) read page 0
+  int32_t blocks;              // query blocks of the longest sequence (the grid has blocks * splits)
+  int32_t splits;              // workgroups that share a block's keys
+  float* lse_part;             // splits > 1: [items, splits, kPrefillRows] (log2 units)
+  float* o_part;               // splits > 1: [items, splits, kPrefillRows, D], item = (b, hk, block)
 };
 
 using PrefillKernelFn = void (*)(PrefillParams);
 // page_size 0 selects the contiguous-cache kernel.
 PrefillKernelFn select_prefill_kernel(int head_dim, int page_size);
+
+constexpr int kPrefillMergeThreads = 256;
+constexpr int kPrefillMergeRows = 16;  // rows per workgroup of the merge kernel
+// Combines the partial results of a split call (grid: blocks * kPrefillRows /
+// kPrefillMergeRows, KV heads, sequences).
+PrefillKernelFn select_prefill_merge_kernel(int head_dim);
 
 }  // namespace comem

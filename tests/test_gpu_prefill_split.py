@@ -1,0 +1,100 @@
+"""Prefill calls whose keys several workgroups share, against the oracle: every split count that a workspace
+size forces, splits that a row or a whole block sees no key of, and the wrapper's own choice."""
+
+import numpy as np
+import pytest
+
+import oracle.prefill_attention as pa
+from tests.gpu_util import DevicePrefill, abs_values, check_prefill, make_op, run_prefill, say
+from workloads.synth import PREFILL_WORKLOADS, generate_prefill, small_prefill_spec
+
+pytestmark = pytest.mark.gpu
+
+
+def _draw(ctx, new, ps, hq=32, hkv=8, d=128, seed=600):
+    base = PREFILL_WORKLOADS[3 if ps else 1]
+    spec = small_prefill_spec(base, ctx, new, seed=seed)
+    kv = spec.kv.replace(num_q_heads=hq, num_kv_heads=hkv, head_dim=d)
+    if ps:
+        kv = kv.replace(page_size=ps)
+    spec = spec.__class__(spec.name, kv, spec.new_tokens, spec.seed)
+    return generate_prefill(spec, **(dict(spare_pages=2, poison=True) if ps else dict(gap_rows=3, poison=True)))
+
+
+def _bytes(items, splits, d):
+    rows = items * splits * 128
+    return -(-rows * 4 // 256) * 256 + rows * d * 4
+
+
+@pytest.mark.parametrize("ps,hq,hkv,d", [(0, 8, 2, 128), (16, 16, 2, 64), (1, 8, 2, 128), (64, 16, 1, 128), (0, 3, 3, 64)])
+def test_every_split_count(ps, hq, hkv, d):
+    """Sequences from all keys new (blocks that see only the first split) to a few over a long prefix, a
+    partial last tile and an empty one, in one call; the workspace's size bounds the splits."""
+    import torch
+
+    import paper_2605_30842_amd.binding as B
+
+    pw = _draw([2500, 700, 1024, 65, 0], [33, 130, 7, 65, 0], ps, hq, hkv, d, seed=601 + ps)
+    dp = DevicePrefill(pw)
+    kv = dp.kv
+    s = pw.kv.spec
+    op = make_op(s)
+    blocks = -(-dp.max_q_len // (128 // s.group))
+    items = s.batch * hkv * blocks
+    want = pa.reference(pw)
+    ref_abs = pa.reference(abs_values(pw))[0]
+    planned = B.comem_prefill_attn_workspace(op.plan, s.batch, dp.max_q_len, s.max_ctx_len)
+    say(f"prefill split: page {ps}, {hq}/{hkv} heads, D {d}, {items} items, planned {planned} bytes")
+    assert planned > 0
+    seen = []
+    for splits in (1, 2, 3, 4, 5):
+        nbytes = _bytes(items, splits, d) if splits > 1 else 0
+        ws = torch.full((max(nbytes, 256),), 0xFF, dtype=torch.uint8, device="cuda:0")  # NaN partials
+        out = torch.full(dp.q.shape, float("nan"), dtype=torch.float32, device="cuda:0")
+        lse = torch.full(dp.q.shape[:2], float("nan"), dtype=torch.float32, device="cuda:0")
+        head = (op.plan, dp.q.data_ptr(), dp.q_start.data_ptr(), dp.q_lens.data_ptr(), dp.max_q_len, kv.k.data_ptr(),
+                kv.v.data_ptr())
+        tail = (s.batch, s.max_ctx_len, out.data_ptr(), lse.data_ptr(), ws.data_ptr(), nbytes,
+                torch.cuda.current_stream().cuda_stream)
+        if ps:
+            B.comem_prefill_attn_split_paged(*head, kv.k.stride(0), kv.k.stride(1), kv.k.stride(2), ps, kv.k.shape[0],
+                                             kv.block_table.data_ptr(), kv.block_table.shape[1],
+                                             kv.ctx_lens.data_ptr(), *tail)
+        else:
+            B.comem_prefill_attn_split(*head, kv.k.stride(0), kv.k.stride(1), kv.seq_start.data_ptr(),
+                                       kv.ctx_lens.data_ptr(), *tail)
+        torch.cuda.synchronize()
+        out, lse = out.cpu().numpy(), lse.cpu().numpy()
+        check_prefill(out, lse, *want, ref_abs, f"{splits} splits")
+        seen.append(out)
+    assert any(not np.array_equal(seen[0], o) for o in seen[1:]), "no workspace size split the keys"
+
+
+@pytest.mark.parametrize("ctx,new,ps", [([9000], [40], 0), ([9000, 3000], [100, 1], 16), ([8192], [8192], 0)])
+def test_wrapper_splits_by_itself(ctx, new, ps):
+    """The wrapper takes its own workspace, on the current and on another stream, and repeats its bits."""
+    import torch
+
+    pw = _draw(ctx, new, ps, 8, 2, 128, seed=620)
+    dp = DevicePrefill(pw)
+    op = make_op(pw.kv.spec)
+    say(f"prefill split wrapper: {ctx} {new} page {ps}")
+    first = run_prefill(dp, op)
+    rows = [(b, i, h) for b, m in enumerate(new) for i in {0, m // 2, m - 1} for h in (0, 7)]
+    ref = pa.prefill_attention_rows(pw, rows)
+    ref_abs = pa.prefill_attention_rows(abs_values(pw), rows)
+    at = [(int(pw.q_start[b]) + i, h) for b, i, h in rows]
+    check_prefill(np.stack([first[0][i, h] for i, h in at]), np.array([first[1][i, h] for i, h in at]),
+                  np.stack([o for o, _ in ref]), np.array([x for _, x in ref]), np.stack([o for o, _ in ref_abs]),
+                  "wrapper")
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    kv, s = dp.kv, pw.kv.spec
+    lse = torch.empty(dp.q.shape[:2], dtype=torch.float32, device="cuda:0")
+    out = torch.empty(dp.q.shape, dtype=torch.float32, device="cuda:0")
+    where = kv.block_table if ps else kv.seq_start
+    call = op.prefill_paged if ps else op.prefill
+    call(dp.q, dp.q_start, dp.q_lens, dp.max_q_len, kv.k, kv.v, where, kv.ctx_lens, s.max_ctx_len, out=out, lse=lse,
+         stream=side)
+    side.synchronize()
+    assert np.array_equal(out.cpu().numpy(), first[0]) and np.array_equal(lse.cpu().numpy(), first[1])

@@ -42,3 +42,40 @@ def test_a_small_workspace_still_gets_every_call():
         assert sizes == sorted(sizes) and sizes[0] == 256 and sizes[-1] >= 8192
     finally:
         B.comem_decode_attn_destroy(p)
+
+
+@pytest.mark.parametrize("kw,status", [
+    (dict(), B.ERR_NO_DEVICE),
+    (dict(workspace=None, workspace_bytes=0), B.ERR_NO_DEVICE),
+    (dict(workspace=(1 << 20) + 16), B.ERR_MISALIGNED),
+    (dict(q=None), B.ERR_NULL_POINTER),
+    (dict(max_q_len=4097), B.ERR_INVALID_SHAPE),
+    (dict(max_q_len=0, q=None), B.OK),
+])
+def test_prefill_split_validation(kw, status):
+    from tests.test_abi import _prefill_args
+
+    p, _ = B.comem_decode_attn_init(_cfg(), B.NO_DEVICE)
+    try:
+        args = _prefill_args(p)
+        stream = args.pop("stream")
+        args.update(workspace=1 << 20, workspace_bytes=1 << 20, stream=stream)
+        args.update(kw)
+        assert B.load_library().comem_prefill_attn_split(*args.values()) == status
+    finally:
+        B.comem_decode_attn_destroy(p)
+
+
+def test_prefill_workspace_sizes():
+    """A few new tokens over a long prefix use a workspace; a grid that fills the GPU, a short context and an
+    empty call do not; a batch past the plan's is refused."""
+    p, _ = B.comem_decode_attn_init(_cfg(max_batch=8, max_ctx_len=65536), B.NO_DEVICE)
+    try:
+        assert B.comem_prefill_attn_workspace(p, 1, 300, 24300) > 0
+        for batch, m, L in ((1, 1024, 32768), (8, 2048, 65536), (1, 8192, 8192), (1, 300, 900), (0, 300, 24300),
+                            (1, 0, 24300)):
+            assert B.comem_prefill_attn_workspace(p, batch, m, L) == 0
+        with pytest.raises(B.ComemError):
+            B.comem_prefill_attn_workspace(p, 9, 300, 24300)
+    finally:
+        B.comem_decode_attn_destroy(p)
