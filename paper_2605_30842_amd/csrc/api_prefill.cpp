@@ -105,13 +105,14 @@ int64_t plan_splits(const comem_decode_attn_plan& p, int64_t batch, int64_t max_
 comem_status launch_prefill(const comem_decode_attn_plan& p, const comem::PrefillParams& a, bool paged,
                             int32_t batch, int32_t max_q_len, void* workspace, size_t workspace_bytes, void* stream) {
   const int64_t blocks = ceil_div(max_q_len, a.tokens_per_block);
-  comem::PrefillKernelFn fn = comem::select_prefill_kernel(p.cfg.head_dim, paged ? a.page_mask + 1 : 0);
-  comem::PrefillKernelFn merge = comem::select_prefill_merge_kernel(p.cfg.head_dim);
-  if (fn == nullptr || merge == nullptr) return COMEM_ERR_UNSUPPORTED;
   comem::PrefillParams args = a;
   args.blocks = static_cast<int32_t>(blocks);
   args.splits = static_cast<int32_t>(
       plan_splits(p, batch, max_q_len, a.max_ctx, workspace == nullptr ? 0 : workspace_bytes));
+  comem::PrefillKernelFn fn =
+      comem::select_prefill_kernel(p.cfg.head_dim, paged ? a.page_mask + 1 : 0, args.splits > 1);
+  comem::PrefillKernelFn merge = comem::select_prefill_merge_kernel(p.cfg.head_dim);
+  if (fn == nullptr || merge == nullptr) return COMEM_ERR_UNSUPPORTED;
   if (args.splits > 1) {
     const size_t rows = static_cast<size_t>(batch * p.cfg.num_kv_heads * blocks) * static_cast<size_t>(args.splits) *
                         comem::kPrefillRows;

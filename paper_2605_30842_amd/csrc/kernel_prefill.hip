@@ -451,7 +451,11 @@ constexpr int kXcds = 8;  // XCDs of the GPU; workgroups are dealt to them round
 // their tiles in ping-pong (one half's products beside the other half's
 // exponentials, see the loop) and merge their softmax states through LDS at
 // the end.
-template <int D, PLayout LAYOUT>
+//
+// SPLIT: the workgroup takes one of p.splits equal shares of the block's keys
+// and leaves a partial result. A form of its own, since the extra scalars
+// spill and cost an unsplit call 0.6%.
+template <int D, PLayout LAYOUT, bool SPLIT>
 __global__ __launch_bounds__(kPrefillThreads, 1) void prefill_mfma_kernel(const PrefillParams p) {
   constexpr int KS = D / 16;
   constexpr int NT = D / 32;
@@ -481,8 +485,8 @@ __global__ __launch_bounds__(kPrefillThreads, 1) void prefill_mfma_kernel(const 
   }
   // The splits of a block's keys: the blocks of one split run side by side,
   // so they share its K/V tiles in L2 like those of an unsplit call.
-  const int split = p.splits > 1 ? q / p.blocks : 0;
-  q -= split * p.blocks;
+  const int split = SPLIT ? q / p.blocks : 0;
+  if constexpr (SPLIT) q -= split * p.blocks;
   const int TB = p.tokens_per_block;
 
   int L = p.ctx_lens[b];
@@ -500,9 +504,9 @@ __global__ __launch_bounds__(kPrefillThreads, 1) void prefill_mfma_kernel(const 
   const int kend = prefix + min(M, i0 + TB);  // keys any row of this block sees
   const int all_tiles = (kend + kPrefillTileKeys - 1) / kPrefillTileKeys;
   // This split's tiles: first_tile .. first_tile + ntiles - 1 (an equal share).
-  const int share = p.splits > 1 ? (all_tiles + p.splits - 1) / p.splits : all_tiles;
+  const int share = SPLIT ? (all_tiles + p.splits - 1) / p.splits : all_tiles;
   const int first_tile = split * share;
-  const int ntiles = min(share, max(all_tiles - first_tile, 0));
+  const int ntiles = SPLIT ? min(share, max(all_tiles - first_tile, 0)) : all_tiles;
   const int nfree = (prefix + i0 + 1) / kPrefillTileKeys;  // tiles visible to every row
 
   const int lane = threadIdx.x & 63;
@@ -671,7 +675,7 @@ __global__ __launch_bounds__(kPrefillThreads, 1) void prefill_mfma_kernel(const 
       // Of an unsplit call half 0 holds key 0, which every row sees; a later
       // split may hold no key that the row sees at all.
       const float mn = fmaxf(m_run, m1);
-      const float a0 = m_run == -INFINITY ? 0.f : fast_exp2((m_run - mn) * p.scale_log2);
+      const float a0 = SPLIT && m_run == -INFINITY ? 0.f : fast_exp2((m_run - mn) * p.scale_log2);
       const float a1 = m1 == -INFINITY ? 0.f : fast_exp2((m1 - mn) * p.scale_log2);
 #pragma unroll
       for (int n = 0; n < NT; ++n)
@@ -693,7 +697,7 @@ __global__ __launch_bounds__(kPrefillThreads, 1) void prefill_mfma_kernel(const 
   float inv = 1.f / l_run;
   const int64_t orow = (qs + i) * p.num_q_heads + qh;
   float* o = p.out + orow * D;
-  if (p.splits > 1) {
+  if constexpr (SPLIT) {
     // Partial result: normalised over the split's keys, with its log-sum-exp
     // in log2 units (0 and -inf if the row sees none of them).
     const int64_t part = prefill_part(p, b, hk, q, split) + row;
@@ -709,7 +713,7 @@ __global__ __launch_bounds__(kPrefillThreads, 1) void prefill_mfma_kernel(const 
       *reinterpret_cast<float4*>(o + 32 * n + 8 * r4 + 4 * h) =
           make_float4(acc[n][4 * r4] * inv, acc[n][4 * r4 + 1] * inv, acc[n][4 * r4 + 2] * inv,
                       acc[n][4 * r4 + 3] * inv);
-  if (h == 0 && p.lse != nullptr && p.splits == 1) p.lse[orow] = (m_run * p.scale_log2 + log2f(l_run)) * kLn2;
+  if (h == 0 && p.lse != nullptr && !SPLIT) p.lse[orow] = (m_run * p.scale_log2 + log2f(l_run)) * kLn2;
 }
 
 // Merge of a split call's partial results. A lane takes 4 head_dim entries
@@ -777,7 +781,9 @@ __global__ __launch_bounds__(kPrefillMergeThreads) void prefill_merge_kernel(con
 
 // Every form the host may launch, instantiated explicitly (clang emitted the
 // host launch stubs of only some of the instantiations referenced below).
-#define COMEM_PREFILL_FORMS(D, L) template __global__ void prefill_mfma_kernel<D, PLayout::L>(const PrefillParams);
+#define COMEM_PREFILL_FORMS(D, L)                                                              \
+  template __global__ void prefill_mfma_kernel<D, PLayout::L, false>(const PrefillParams); \
+  template __global__ void prefill_mfma_kernel<D, PLayout::L, true>(const PrefillParams);
 COMEM_PREFILL_FORMS(128, kContig)
 COMEM_PREFILL_FORMS(128, kPaged)
 COMEM_PREFILL_FORMS(128, kPagedFine)
@@ -790,14 +796,14 @@ template __global__ void prefill_merge_kernel<64>(const PrefillParams);
 
 }  // namespace
 
-template <int D>
+template <int D, bool SPLIT>
 PrefillKernelFn prefill_by_layout(int page_size) {
   // page_size 0: contiguous cache. A paged cache takes the per-group path when
   // a wave's 16-row group of a tile fits in a page (it starts at a multiple of
   // 16 for either head_dim).
-  PrefillKernelFn fn = prefill_mfma_kernel<D, PLayout::kPagedFine>;
-  if (page_size == 0) fn = prefill_mfma_kernel<D, PLayout::kContig>;
-  else if (page_size >= 16) fn = prefill_mfma_kernel<D, PLayout::kPaged>;
+  PrefillKernelFn fn = prefill_mfma_kernel<D, PLayout::kPagedFine, SPLIT>;
+  if (page_size == 0) fn = prefill_mfma_kernel<D, PLayout::kContig, SPLIT>;
+  else if (page_size >= 16) fn = prefill_mfma_kernel<D, PLayout::kPaged, SPLIT>;
   return fn;
 }
 
@@ -805,9 +811,9 @@ PrefillKernelFn select_prefill_merge_kernel(int head_dim) {
   return head_dim == 128 ? prefill_merge_kernel<128> : (head_dim == 64 ? prefill_merge_kernel<64> : nullptr);
 }
 
-PrefillKernelFn select_prefill_kernel(int head_dim, int page_size) {
-  if (head_dim == 128) return prefill_by_layout<128>(page_size);
-  if (head_dim == 64) return prefill_by_layout<64>(page_size);
+PrefillKernelFn select_prefill_kernel(int head_dim, int page_size, bool split) {
+  if (head_dim == 128) return split ? prefill_by_layout<128, true>(page_size) : prefill_by_layout<128, false>(page_size);
+  if (head_dim == 64) return split ? prefill_by_layout<64, true>(page_size) : prefill_by_layout<64, false>(page_size);
   return nullptr;
 }
 

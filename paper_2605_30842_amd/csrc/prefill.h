@@ -43,7 +43,7 @@ struct PrefillParams {
 
 using PrefillKernelFn = void (*)(PrefillParams);
 // page_size 0 selects the contiguous-cache kernel.
-PrefillKernelFn select_prefill_kernel(int head_dim, int page_size);
+PrefillKernelFn select_prefill_kernel(int head_dim, int page_size, bool split);
 
 constexpr int kPrefillMergeThreads = 256;
 constexpr int kPrefillMergeRows = 16;  // rows per workgroup of the merge kernel
