@@ -403,6 +403,13 @@ def _check_tensor(name, t, dtypes, device, shape=None, ndim=None, contiguous=Tru
         _need(t.is_contiguous(), f"{name} must be contiguous")
 
 
+def _fits(t, tensor, dtypes, device, shape) -> bool:
+    """True only if _check_tensor would pass t as a contiguous tensor of this shape (the common case, in one
+    expression: the checks of a call took 20-25 us on the host, several times as long as a short kernel)."""
+    return (isinstance(t, tensor) and t.dtype in dtypes and t.device == device and t.shape == shape
+            and t.is_contiguous())
+
+
 # ------------------------------------------------------------ torch wrapper
 
 
@@ -488,18 +495,33 @@ class DecodeAttention:
     # Checks of every tensor against the plan, before any pointer reaches the library.
 
     def _check_q_out(self, q, out, lse, rows=None):
-        Hq, D = self.num_q_heads, self.head_dim
-        _check_tensor("q", q, self._q_dtypes, self._torch_device, shape=(rows, Hq, D))
-        R = q.shape[0]
         import torch
 
+        Hq, D = self.num_q_heads, self.head_dim
+        tensor, dev = torch.Tensor, self._torch_device
+        if rows is None and isinstance(q, tensor) and q.dim() > 0:
+            R, f32 = q.shape[0], (torch.float32,)
+            if (_fits(q, tensor, self._q_dtypes, dev, (R, Hq, D))
+                    and (out is None or _fits(out, tensor, f32, dev, (R, Hq, D)))
+                    and (lse is None or _fits(lse, tensor, f32, dev, (R, Hq)))):
+                return
+        _check_tensor("q", q, self._q_dtypes, self._torch_device, shape=(rows, Hq, D))
+        R = q.shape[0]
         if out is not None:
             _check_tensor("out", out, (torch.float32,), self._torch_device, shape=(R, Hq, D))
         if lse is not None:
             _check_tensor("lse", lse, (torch.float32,), self._torch_device, shape=(R, Hq))
 
     def _check_cache(self, k, v, paged: bool):
+        import torch
+
         dims = 4 if paged else 3
+        if isinstance(k, torch.Tensor) and isinstance(v, torch.Tensor):
+            shape, strides, dev = k.shape, k.stride(), self._torch_device
+            if (len(shape) == dims and shape == v.shape and strides == v.stride() and strides[-1] == 1
+                    and shape[-2] == self.num_kv_heads and shape[-1] == self.head_dim
+                    and k.dtype in self._kv_dtypes and k.dtype == v.dtype and k.device == dev and v.device == dev):
+                return
         for name, t in (("k", k), ("v", v)):
             _check_tensor(name, t, self._kv_dtypes, self._torch_device, ndim=dims, contiguous=False)
             _need(t.shape[-2] == self.num_kv_heads and t.shape[-1] == self.head_dim,
@@ -511,6 +533,12 @@ class DecodeAttention:
     def _check_lengths(self, ctx_lens, batch, seq_start=None, block_table=None):
         import torch
 
+        tensor, dev, i32 = torch.Tensor, self._torch_device, (torch.int32,)
+        if (_fits(ctx_lens, tensor, i32, dev, (batch,))
+                and (seq_start is None or _fits(seq_start, tensor, (torch.int64,), dev, (batch,)))
+                and (block_table is None or (isinstance(block_table, tensor) and block_table.dim() == 2
+                                             and _fits(block_table, tensor, i32, dev, (batch, block_table.shape[1]))))):
+            return
         _check_tensor("ctx_lens", ctx_lens, (torch.int32,), self._torch_device, shape=(batch,))
         if seq_start is not None:
             _check_tensor("seq_start", seq_start, (torch.int64,), self._torch_device, shape=(batch,))
@@ -518,29 +546,43 @@ class DecodeAttention:
             _check_tensor("block_table", block_table, (torch.int32,), self._torch_device, shape=(batch, None))
 
     def _check_new_rows(self, new_k, new_v, k, batch):
+        import torch
+
+        if batch is not None or (isinstance(new_k, torch.Tensor) and new_k.dim() > 0):
+            rows = new_k.shape[0] if batch is None else batch
+            shape, dtypes = (rows, self.num_kv_heads, self.head_dim), (k.dtype,)
+            if (_fits(new_k, torch.Tensor, dtypes, self._torch_device, shape)
+                    and _fits(new_v, torch.Tensor, dtypes, self._torch_device, shape)):
+                return
         for name, t in (("new_k", new_k), ("new_v", new_v)):
             _check_tensor(name, t, (k.dtype,), self._torch_device, shape=(batch, self.num_kv_heads, self.head_dim))
 
     @staticmethod
     def _check_bound(max_ctx_len, name="max_ctx_len"):
+        if type(max_ctx_len) is int:
+            return
         import numbers
 
         _need(isinstance(max_ctx_len, numbers.Integral) and not isinstance(max_ctx_len, bool),
               f"{name} must be an integer, got {type(max_ctx_len).__name__}")
 
     def _outputs(self, q, out, lse):
-        import torch
-
-        B, Hq, D = q.shape
         if out is None:
-            out = torch.empty((B, Hq, D), dtype=torch.float32, device=q.device)
+            import torch
+
+            out = torch.empty(q.shape, dtype=torch.float32, device=q.device)
         return out, lse
 
     @staticmethod
     def _stream(stream):
+        if stream is not None:
+            return stream.cuda_stream
         import torch
 
-        return (stream if stream is not None else torch.cuda.current_stream()).cuda_stream
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # the same handle without a Stream object
+        if raw is None:
+            return torch.cuda.current_stream().cuda_stream
+        return raw(torch.cuda.current_device())
 
     def forward(self, q, k, v, seq_start, ctx_lens, max_ctx_len: int, out=None, lse=None, stream=None):
         self._check_q_out(q, out, lse)
@@ -625,6 +667,15 @@ class DecodeAttention:
     def _check_prefill(self, q, q_start, q_lens, max_q_len, ctx_lens, out, lse, max_ctx_len):
         import torch
 
+        tensor, dev, i32 = torch.Tensor, self._torch_device, (torch.int32,)
+        if isinstance(ctx_lens, tensor) and ctx_lens.dim() == 1:
+            shape = (ctx_lens.shape[0],)
+            if (_fits(ctx_lens, tensor, i32, dev, shape) and _fits(q_lens, tensor, i32, dev, shape)
+                    and _fits(q_start, tensor, (torch.int64,), dev, shape)):
+                self._check_q_out(q, out, lse)
+                self._check_bound(max_q_len, "max_q_len")
+                self._check_bound(max_ctx_len)
+                return
         _check_tensor("ctx_lens", ctx_lens, (torch.int32,), self._torch_device, ndim=1)
         batch = ctx_lens.shape[0]
         self._check_q_out(q, out, lse)
