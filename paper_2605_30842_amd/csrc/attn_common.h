@@ -92,7 +92,7 @@ template <int D>
 struct WaveState {
   float m[kWaves][kMaxGroup];   // running max (log2 units), -inf if no token seen
   float l[kWaves][kMaxGroup];   // sum of exp2(x - m)
-  alignas(16) float o[kWaves][kMaxGroup][D];  // sum of exp2(x - m) * v
+  alignas(16) float o[kWaves][kMaxGroup][D + 4];  // sum of exp2(x - m) * v (rows 4 banks apart)
 };
 
 __device__ inline int64_t uniform_i64(int64_t x) {

@@ -8,7 +8,7 @@
 // (16 tokens x 16 head columns per instruction; the G real heads of the GQA
 // group occupy the first G columns), runs the online softmax on the scores
 // in registers, and accumulates
-//   O[head, d] += P[head, token] . V_tile[token, d]
+//   O^T[d, head] += V_tile^T[d, token] . P^T[token, head]
 // again with 16x16x32 MFMAs. P is split as P = P_hi + P_lo, both bf16, and
 // both halves are multiplied (two MFMAs), so the weights keep about 17
 // significant bits instead of bf16's 8.
@@ -21,13 +21,15 @@
 //        32kb + 8g .. +8 -> one 16-byte load per (sub-tile, kb).
 //        B = Q rows (head c), same slice. Result: lane holds the score of
 //        head c for tokens 4g + r of each 16-token sub-tile.
-//   PV:  A = P: lane already holds head c's weights for the 8 tokens
+//   PV:  B = P^T: lane already holds head c's weights for the 8 tokens
 //        {16s + 4g + r}; they become reduction elements e = 4s + r.
-//        B = V: the same 8 tokens, column c standing for d = NT*c + n in
+//        A = V^T: the same 8 tokens, row c standing for d = NT*c + n in
 //        n-tile n (NT = D/16). Loading V row (16s + 4g + r), bytes
 //        [2*NT*c, 2*NT*(c+1)) gives every n-tile's element at once, and
 //        those loads read whole 256-byte rows with 16 consecutive lanes.
 //        A v_perm per element pair regroups them into MFMA operands.
+//        Result: lane holds head c at d = NT*(4g + r) + n, so its maximum,
+//        sum and rescaling are those of its own head.
 // The reduction index of an MFMA is a dummy index, so any consistent
 // assignment of (lane, element) to tokens or head_dim positions is valid as
 // long as A and B use the same one, which they do by construction above.
@@ -296,6 +298,27 @@ struct Loader {
   }
 };
 
+// The larger (or the sum) of the four lane groups' values of x, in every
+// lane: row and half swaps in the vector unit, where a shuffle through LDS
+// takes a round trip of about 100 cycles in the middle of a tile's one chain.
+struct Max {
+  __device__ float operator()(float a, float b) const { return fmaxf(a, b); }
+};
+struct Add {
+  __device__ float operator()(float a, float b) const { return a + b; }
+};
+template <typename Op>
+__device__ inline float across_groups(float x, Op op) {
+  const uint32_t u = __float_as_uint(x);
+  const auto rows = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const uint32_t v = __float_as_uint(op(__uint_as_float(rows[0]), __uint_as_float(rows[1])));
+  const auto halves = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return op(__uint_as_float(halves[0]), __uint_as_float(halves[1]));
+}
+
+// With one wave on a SIMD (short calls, and the balanced form) a tile's time
+// is this chain's latency: scores, maximum, weights, products. So nothing in
+// it goes through LDS, and the outputs are rescaled only when a maximum moved.
 template <int D>
 __device__ inline void compute_tile(const Tile<D>& T, int t0, int t_end, int g,
                                     const bf16x8 (&qop)[D / 32], float scale_log2, float& m_run,
@@ -322,21 +345,15 @@ __device__ inline void compute_tile(const Tile<D>& T, int t0, int t_end, int g,
       x[4 * s + r] = v;
       mt = fmaxf(mt, v);
     }
-  mt = fmaxf(mt, __shfl_xor(mt, 16));
-  mt = fmaxf(mt, __shfl_xor(mt, 32));
-  // Every tile holds at least one valid token, so m_new is finite.
-  const float m_new = fmaxf(m_run, mt);
-  const float alpha = fast_exp2(m_run - m_new);
-  {
-    float ar[4];
+  // Every tile holds at least one valid token, so the new maximum is finite.
+  const float m_new = fmaxf(m_run, across_groups(mt, Max{}));
+  if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
+    const float alpha = fast_exp2(m_run - m_new);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) ar[r] = __shfl(alpha, 4 * g + r);
-#pragma unroll
-    for (int n = 0; n < NT; ++n)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc[n][r] *= ar[r];
+    for (int n = 0; n < NT; ++n) acc[n] *= alpha;
+    l_run *= alpha;
+    m_run = m_new;
   }
-  m_run = m_new;
   float psum = 0.f;
   uint32_t ph[4], pl[4];
 #pragma unroll
@@ -346,20 +363,20 @@ __device__ inline void compute_tile(const Tile<D>& T, int t0, int t_end, int g,
     psum += p0 + p1;
     split_bf16(p0, p1, ph[e / 2], pl[e / 2]);
   }
-  l_run = l_run * alpha + psum;
-  const bf16x8 pa_hi = as_bf16x8(u32x4{ph[0], ph[1], ph[2], ph[3]});
-  const bf16x8 pa_lo = as_bf16x8(u32x4{pl[0], pl[1], pl[2], pl[3]});
+  l_run += psum;
+  const bf16x8 p_hi = as_bf16x8(u32x4{ph[0], ph[1], ph[2], ph[3]});
+  const bf16x8 p_lo = as_bf16x8(u32x4{pl[0], pl[1], pl[2], pl[3]});
 #pragma unroll
   for (int n = 0; n < NT; ++n) {
     const uint32_t sel = (n & 1) ? 0x07060302u : 0x05040100u;
     const int wi = n >> 1;
-    u32x4 vb;
-    vb[0] = __builtin_amdgcn_perm(T.v[0][1].word(wi), T.v[0][0].word(wi), sel);
-    vb[1] = __builtin_amdgcn_perm(T.v[0][3].word(wi), T.v[0][2].word(wi), sel);
-    vb[2] = __builtin_amdgcn_perm(T.v[1][1].word(wi), T.v[1][0].word(wi), sel);
-    vb[3] = __builtin_amdgcn_perm(T.v[1][3].word(wi), T.v[1][2].word(wi), sel);
-    acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa_hi, as_bf16x8(vb), acc[n], 0, 0, 0);
-    acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa_lo, as_bf16x8(vb), acc[n], 0, 0, 0);
+    u32x4 va;
+    va[0] = __builtin_amdgcn_perm(T.v[0][1].word(wi), T.v[0][0].word(wi), sel);
+    va[1] = __builtin_amdgcn_perm(T.v[0][3].word(wi), T.v[0][2].word(wi), sel);
+    va[2] = __builtin_amdgcn_perm(T.v[1][1].word(wi), T.v[1][0].word(wi), sel);
+    va[3] = __builtin_amdgcn_perm(T.v[1][3].word(wi), T.v[1][2].word(wi), sel);
+    acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(va), p_hi, acc[n], 0, 0, 0);
+    acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(va), p_lo, acc[n], 0, 0, 0);
   }
 }
 
@@ -500,23 +517,20 @@ __device__ void attend_split(const AttnParams& p, WaveState<D>& ws, int b, int h
     *next_item = static_cast<int>(gridDim.x + atomicAdd(p.tickets + p.queue_slot, 1u));
 
   // Wave totals: l over the four lane groups; state to LDS.
-  l_run += __shfl_xor(l_run, 16);
-  l_run += __shfl_xor(l_run, 32);
+  l_run = across_groups(l_run, Add{});
   if (g == 0 && c < G) {
     ws.m[w][c] = m_run;
     ws.l[w][c] = l_run;
   }
-  // A lane's values of one head are NT consecutive head_dim positions, so
-  // they go out as 16-byte stores.
+  // A lane holds head c at NT consecutive head_dim positions per r: 16-byte
+  // stores.
+  if (c < G) {
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int h = 4 * g + r;
-    if (h < G) {
+    for (int r = 0; r < 4; ++r)
 #pragma unroll
       for (int n = 0; n < NT; n += 4)
-        *reinterpret_cast<float4*>(&ws.o[w][h][NT * c + n]) =
+        *reinterpret_cast<float4*>(&ws.o[w][c][NT * (4 * g + r) + n]) =
             make_float4(acc[n][r], acc[n + 1][r], acc[n + 2][r], acc[n + 3][r]);
-    }
   }
   __syncthreads();
   finalize_split<D>(p, ws, b, hk, parts);
