@@ -144,16 +144,19 @@ int64_t long_chunk(const comem_decode_attn_plan& p, int64_t batch, int64_t L) {
 }
 
 // Long calls of several sequences take the balanced form, short ones one
-// workgroup per split. A range pays for every piece it holds with a merge
-// and a pipeline to refill (about 2048 tokens' worth of reading, and its
-// kernel starts 2 us later); the equal shares win that back once a range is
-// long. Measured (us, bf16, 8 KV heads, G = 4, lengths from a quarter of the
-// bound up, balanced / best splits): 8 x 16384 tokens 51.3 / 55.9, 16 x 8192
-// 51.7 / 57.6, 32 x 4096 53.4 / 59.3, 64 x 4096 114 / 132; on the other side
-// 8 x 8192 31.2 / 30.7, 64 x 1024 36.0 / 32.5, 128 x 1024 63.9 / 57.3, 128 x
-// 2048 124.6 / 120.9.
+// workgroup per split. The balanced kernel starts 1-2 us later, and a range
+// pays for every piece it holds; its equal shares win that back once ranges
+// are long. Swept over 2-128 sequences, 2-8 KV heads, bf16 and FP8, head_dim
+// 64 and 128, lengths from 0.15, 0.5 and 1 of the bound up (best splits /
+// balanced): at 900-1000 tokens of bound per range and sequence 0.87-1.05, at
+// 1365 0.94-1.27, at 1638-1820 0.96-1.27, from 2700 0.97-1.35. With a pair of
+// sequence and head for every compute unit, unsplit sequences end evenly
+// enough by themselves: at 1365 0.88-1.08, at 1638 (512-byte tokens)
+// 1.00-1.08, and lighter tokens, whose pieces cost relatively more, at 1638
+// 0.92-1.04, at 2048 0.96-1.09.
 bool long_call(const comem_decode_attn_plan& p, int64_t batch, int64_t L) {
-  const int64_t tokens = batch * p.cfg.num_kv_heads >= p.num_cus ? 2048 : 1024;
+  const bool light = p.cfg.head_dim * elem_bytes(p.cfg) <= 128;
+  const int64_t tokens = batch * p.cfg.num_kv_heads < p.num_cus ? 1200 : (light ? 2048 : 1600);
   return batch * L >= tokens * (max_ranges(p) + batch);
 }
 
@@ -253,7 +256,8 @@ bool uses_balanced(const comem_decode_attn_plan& p, int64_t batch, int64_t max_c
                    size_t ws_bytes, size_t ticket_region) {
   return uses_mfma(p) && p.cfg.variant != COMEM_VARIANT_MFMA_GRID && p.cfg.chunk_tokens == 0 &&
          (batch == 1 || long_call(p, batch, max_ctx)) && batch <= comem::mfma_max_queue_batch() &&
-         workspace != nullptr && ws_bytes >= ticket_region + balanced_bytes(p) && batch * ceil_div(max_ctx + 1, 32) < kMaxBalancedTiles;
+         workspace != nullptr && ws_bytes >= ticket_region + balanced_bytes(p) &&
+         batch * (ceil_div(max_ctx + 1, 32) + comem::kPieceTilesLight) < kMaxBalancedTiles;
 }
 
 comem_status launch_balanced(const comem_decode_attn_plan& p, bool paged, comem::AttnParams& a, int64_t batch,

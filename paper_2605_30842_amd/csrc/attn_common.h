@@ -25,6 +25,9 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 constexpr int kWaves = 4;           // waves per workgroup
 constexpr int kThreads = 64 * kWaves;
 constexpr int kMaxGroup = 16;       // largest GQA group handled in one workgroup
+// Balanced form: units a sequence counts besides its 32-token tiles (of 512
+// bytes a token and head, or of 256 and less).
+constexpr int kPieceTiles = 8, kPieceTilesLight = 12;
 constexpr float kLn2 = 0.69314718055994530942f;
 
 // Kernel arguments (passed by value). Offsets and strides are in bytes.

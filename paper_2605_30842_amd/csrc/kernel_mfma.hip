@@ -673,6 +673,10 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_queue_kernel(const At
 // (hk, r) attends over range r of KV head hk, in one piece per sequence that
 // the range touches. A sequence inside one range is written directly; the
 // pieces of one that several ranges share are merged by the last to finish.
+// A second piece costs a workgroup a merge and a pipeline to refill, about
+// the time of kPieceTiles tiles, so each sequence counts that many units
+// before its tiles (us without / with: 8 fp8 sequences of 1000-7000 tokens
+// 18.5 / 16.7, 8 bf16 of 2000-8192 36.3 / 34.9, 4 of 5000-32768 63.0 / 61.4).
 //
 // HBM bandwidth bounds it, and one workgroup per CU with one long equal piece
 // of work reads faster than more, shorter items: fewer times does a workgroup
@@ -693,11 +697,12 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_queue_kernel(const At
 template <int D, Layout LAYOUT, bool FP8>
 __global__ __launch_bounds__(kThreads, 2) void decode_mfma_balanced_kernel(const AttnParams p, int batch) {
   __shared__ WaveState<D> ws;
-  __shared__ int sm_first[kMaxQueueBatch + 1];  // batches over 64: prefix sums of tiles per sequence
+  __shared__ int sm_first[kMaxQueueBatch + 1];  // batches over 64: prefix sums of units per sequence
+  constexpr int kPiece = FP8 || D == 64 ? kPieceTilesLight : kPieceTiles;
   const int hk = blockIdx.x, r = blockIdx.y;
   const int lane = threadIdx.x & 63;
-  // Tiles per sequence (an empty one has one, empty, tile) as prefix sums:
-  // up to 64 sequences in the lanes of every wave, else in LDS.
+  // Units per sequence as prefix sums: up to 64 sequences in the lanes of
+  // every wave, else in LDS.
   const bool in_lanes = batch <= 64;
   int len = 0, incl = 0, total;
   int64_t row = 0;  // seq_start, requested together with the length
@@ -706,7 +711,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_balanced_kernel(const
       len = p.ctx_lens[lane];
       if constexpr (LAYOUT == Layout::kContig) row = p.seq_start[lane];
       len = checked_len(len, p.max_ctx, p.errors);
-      incl = tiles_of(len);
+      incl = kPiece + tiles_of(len);
     }
     for (int o = 1; o < batch; o <<= 1) {
       const int u = __shfl_up(incl, o);
@@ -715,7 +720,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_balanced_kernel(const
     total = __builtin_amdgcn_readlane(incl, batch - 1);
   } else {
     for (int b = threadIdx.x; b < batch; b += kThreads)
-      sm_first[b + 1] = tiles_of(checked_len(p.ctx_lens[b], p.max_ctx, p.errors));
+      sm_first[b + 1] = kPiece + tiles_of(checked_len(p.ctx_lens[b], p.max_ctx, p.errors));
     __syncthreads();
     if (threadIdx.x < 64) wave_prefix_sum(sm_first, batch, lane);
     __syncthreads();
@@ -741,11 +746,13 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_balanced_kernel(const
     } else {
       load_sequence<LAYOUT>(p, b, L, seq_row);
     }
-    const int piece_end = min(stop, end);
-    const int r0 = uniform_i32(static_cast<int>(div_small(first, per, rper)));
-    const int r1 = uniform_i32(static_cast<int>(div_small(end - 1, per, rper)));
-    attend_split<D, LAYOUT, FP8>(p, ws, b, hk, RangeParts(p, hk, r, r0, r1), 32 * (cur - first),
-                                 min(L, 32 * (piece_end - first)), L, seq_row, nullptr);
+    const int piece_end = min(stop, end), begin = first + kPiece;
+    if (piece_end > begin) {
+      const int r0 = uniform_i32(static_cast<int>(div_small(begin, per, rper)));
+      const int r1 = uniform_i32(static_cast<int>(div_small(end - 1, per, rper)));
+      attend_split<D, LAYOUT, FP8>(p, ws, b, hk, RangeParts(p, hk, r, r0, r1), 32 * max(cur - begin, 0),
+                                   min(L, 32 * (piece_end - begin)), L, seq_row, nullptr);
+    }
     cur = piece_end;
     if (cur >= stop) return;
     ++b;
