@@ -138,10 +138,9 @@ const char* comem_status_string(comem_status status);
 
 /* Tokens per split and number of splits a call would use (for tests and
  * reports): same planning as the contiguous compute call. A paged call with
- * pages of 1 or 2 tokens may plan shorter splits, so that the block-table
- * entries of one split fit the matrix-core kernel's on-chip copy (2048
- * entries); a configured chunk_tokens that does not fit is refused with
- * COMEM_ERR_INVALID_SHAPE. A sequence of L tokens has ceil(L / chunk)
+ * pages of 1 or 2 tokens may plan shorter splits, so that a split spans at
+ * most 2048 block-table entries; a configured chunk_tokens that spans more
+ * is refused with COMEM_ERR_INVALID_SHAPE. A sequence of L tokens has ceil(L / chunk)
  * splits, except that a matrix-core call with chunk_tokens = 0, a workspace
  * of the size comem_decode_attn_init reports and either one sequence or a
  * long bound (batch * max_ctx_len of a thousand tokens and more for every

@@ -700,12 +700,15 @@ class DecodeAttention:
         if max_ctx_len < PREFILL_SPLIT_MIN_CTX:
             return None
         nbytes = comem_prefill_attn_workspace(self.plan, batch, max_q_len, max_ctx_len)
-        if nbytes == 0:
+        if nbytes == 0 or not (stream is None or isinstance(stream, torch.cuda.Stream)):
             return None
-        if stream is None:
-            return torch.empty(nbytes, dtype=torch.uint8, device=self._torch_device)
-        with torch.cuda.stream(stream):
-            return torch.empty(nbytes, dtype=torch.uint8, device=self._torch_device)
+        try:
+            if stream is None:
+                return torch.empty(nbytes, dtype=torch.uint8, device=self._torch_device)
+            with torch.cuda.stream(stream):
+                return torch.empty(nbytes, dtype=torch.uint8, device=self._torch_device)
+        except torch.OutOfMemoryError:  # the call needs no scratch
+            return None
 
     def prefill(self, q, q_start, q_lens, max_q_len: int, k, v, seq_start, ctx_lens, max_ctx_len: int, out=None,
                 lse=None, stream=None):

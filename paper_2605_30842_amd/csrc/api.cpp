@@ -176,7 +176,7 @@ int64_t short_chunk(const comem_decode_attn_plan& p, int64_t batch, int64_t L) {
 
 // Choose tokens per split and the split count for one call. page_size is 0
 // for a contiguous cache; for a paged one the matrix-core kernel's planned
-// splits stay within the pages its LDS copy of the block table holds.
+// splits stay within kMaxSplitPages entries.
 comem_status plan_call(const comem_decode_attn_plan& p, int64_t batch, int64_t max_ctx, int64_t page_size,
                        size_t ws_bytes, int64_t* chunk_out, int64_t* splits_out) {
   const int64_t L = max_ctx > 0 ? max_ctx : 1;
@@ -233,10 +233,6 @@ comem_status validate_config(const comem_decode_attn_config& c) {
   }
   return COMEM_OK;
 }
-
-
-
-
 
 bool uses_mfma(const comem_decode_attn_plan& p) {
   return p.cfg.variant == COMEM_VARIANT_MFMA || p.cfg.variant == COMEM_VARIANT_MFMA_GRID ||
@@ -523,7 +519,8 @@ comem_status comem_decode_attn_init(const comem_decode_attn_config* cfg, int dev
   p->ticket_shift = choose_ticket_shift(num_tickets(*p));
   p->ticket_bytes = ticket_region_bytes(num_tickets(*p), p->ticket_shift);
   // Largest number of (sequence, split) slots any call within the limits plans
-  // (bounded for the matrix-core kernel by its smallest split of 1024 tokens);
+  // (for the matrix-core kernel: splits of 1024 tokens, or, of short calls, one
+  // per compute unit);
   // calls with a smaller workspace get coarser splits.
   const int64_t B = cfg->max_batch, L = cfg->max_ctx_len;
   int64_t slots;

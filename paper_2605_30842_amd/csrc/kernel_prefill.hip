@@ -699,11 +699,12 @@ __global__ __launch_bounds__(kPrefillThreads, 1) void prefill_mfma_kernel(const 
   float* o = p.out + orow * D;
   if constexpr (SPLIT) {
     // Partial result: normalised over the split's keys, with its log-sum-exp
-    // in log2 units (0 and -inf if the row sees none of them).
+    // in log2 units (0 and -inf if the row sees none of them; a sum of NaN
+    // stays one, so the row's lse is NaN as in an unsplit call).
     const int64_t part = prefill_part(p, b, hk, q, split) + row;
     o = p.o_part + part * D;
-    if (!(l_run > 0.f)) inv = 0.f;
-    if (h == 0) p.lse_part[part] = l_run > 0.f ? m_run * p.scale_log2 + log2f(l_run) : -INFINITY;
+    if (l_run == 0.f) inv = 0.f;
+    if (h == 0) p.lse_part[part] = l_run == 0.f ? -INFINITY : m_run * p.scale_log2 + log2f(l_run);
   }
   // acc[n] register r holds head_dim 32 n + 8 (r / 4) + 4 h + r % 4.
 #pragma unroll

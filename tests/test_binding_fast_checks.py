@@ -70,3 +70,17 @@ def test_group_checks_agree_with_and_without_the_short_form(monkeypatch):
     monkeypatch.setattr(B, "_fits", lambda *a: False)
     assert [_passes(f, *a) for f, a in calls] == short
     assert any(short) and not all(short)
+
+
+def test_prefill_without_scratch_when_it_cannot_be_had(monkeypatch):
+    """Prefill scratch is an option: a full device or a foreign stream object leaves the call without it."""
+    op = _op()
+    monkeypatch.setattr(B, "comem_prefill_attn_workspace", lambda *a: 512)
+    assert op._prefill_workspace(1, 40, 9000, None).numel() == 512
+    assert op._prefill_workspace(1, 40, 9000, type("S", (), {"cuda_stream": 0})()) is None
+
+    def full(*a, **kw):
+        raise torch.OutOfMemoryError("full")
+
+    monkeypatch.setattr(torch, "empty", full)
+    assert op._prefill_workspace(1, 40, 9000, None) is None

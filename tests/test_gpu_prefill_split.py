@@ -98,3 +98,17 @@ def test_wrapper_splits_by_itself(ctx, new, ps):
          stream=side)
     side.synchronize()
     assert np.array_equal(out.cpu().numpy(), first[0]) and np.array_equal(lse.cpu().numpy(), first[1])
+
+
+def test_nan_key_reaches_out_and_lse():
+    """A NaN key in one split's share makes the rows that see it NaN, outputs and lse, as in an unsplit call."""
+    import torch
+
+    pw = _draw([9000], [40], 0, 8, 2, 128, seed=630)
+    dp = DevicePrefill(pw)
+    kv, op = dp.kv, make_op(pw.kv.spec)
+    say("prefill split: a NaN key")
+    kv.k[int(pw.kv.seq_start[0]) + 4000, 1, 5] = float("nan")
+    out, lse = (torch.from_numpy(x) for x in run_prefill(dp, op))
+    assert out[:, 4:].isnan().all() and lse[:, 4:].isnan().all()
+    assert out[:, :4].isfinite().all() and lse[:, :4].isfinite().all()
