@@ -141,13 +141,14 @@ const char* comem_status_string(comem_status status);
  * pages of 1 or 2 tokens may plan shorter splits, so that a split spans at
  * most 2048 block-table entries; a configured chunk_tokens that spans more
  * is refused with COMEM_ERR_INVALID_SHAPE. A sequence of L tokens has ceil(L / chunk)
- * splits, except that a matrix-core call with chunk_tokens = 0, a workspace
- * of the size comem_decode_attn_init reports and either one sequence or a
- * long bound (batch * max_ctx_len of a thousand tokens and more for every
- * compute unit and sequence) cuts the tokens of all its sequences into equal
- * ranges of whole 32-token tiles: the boundaries of a sequence's splits then
- * follow from the lengths of all sequences in the call. Nothing depends on
- * timing, so the same call always returns the same bits. */
+ * splits, except that a matrix-core call with chunk_tokens = 0 and a
+ * workspace of the size comem_decode_attn_init reports shares the 32-token
+ * tiles out differently: of one sequence, split j of n takes the tiles j,
+ * j + n, ...; of several with a long bound (batch * max_ctx_len of a thousand
+ * tokens and more for every compute unit and sequence), the tiles of all
+ * sequences are cut into equal ranges, so that a sequence's splits follow
+ * from the lengths of all sequences in the call. Nothing depends on timing:
+ * the same call always returns the same bits. */
 comem_status comem_decode_attn_plan_splits(const comem_decode_attn_plan* plan, int32_t batch,
                                            int64_t max_ctx_len, size_t workspace_bytes,
                                            int32_t* chunk_tokens_out, int32_t* num_splits_out);

@@ -168,6 +168,7 @@ struct Loader {
   int64_t stride_page;
   int page_shift, page_mask;
   int t_first;  // the wave's first tile
+  int t_step;   // tokens from one of its tiles to the next
   int t_end;
   int lane, c, g;
   uint32_t koff;     // c * stride_token + 16 g (FP8: + (D / 4) g)
@@ -196,8 +197,8 @@ struct Loader {
   __device__ int32_t entry_of(int t) const { return bt_row[min(t, t_end - 1) >> page_shift]; }
   // Entries of the wave's tiles n .. n + 31 (n a multiple of 32), or of its tile n.
   __device__ int32_t entries(int n) const {
-    if constexpr (LAYOUT == Layout::kPaged) return entry_of(t_first + 32 * kWaves * (n + (lane >> 1)) + 16 * (lane & 1));
-    return entry_of(t_first + 32 * kWaves * n + (lane & 31));
+    if constexpr (LAYOUT == Layout::kPaged) return entry_of(t_first + t_step * (n + (lane >> 1)) + 16 * (lane & 1));
+    return entry_of(t_first + t_step * n + (lane & 31));
   }
   __device__ void first_entries() {
     if constexpr (LAYOUT == Layout::kPaged) {
@@ -407,8 +408,9 @@ __device__ inline void load_sequence(const AttnParams& p, int b, int& L, int64_t
 }
 
 // Attention of the G query heads of KV head hk of sequence b over one split
-// (tokens [t_begin, t_end), t_begin a multiple of 32), ending with this
-// split's share of the log-sum-exp merge. Called by every thread of the
+// (its `ntiles` tiles of 32 tokens, `stride` tokens from one to the next, from
+// token t_begin, a multiple of 32, on; the last may end early at t_end),
+// ending with this split's share of the log-sum-exp merge. Called by every thread of the
 // workgroup. seq_row is seq_start[b] for the contiguous layout (unused when
 // paged); the callers load it together with ctx_lens[b], so the two loads
 // cost one round trip before the first tile is requested.
@@ -418,7 +420,7 @@ __device__ inline void load_sequence(const AttnParams& p, int b, int& L, int64_t
 // atomic would sit ahead of the tile loads in the in-order memory counter.
 template <int D, Layout LAYOUT, bool FP8, typename Parts>
 __device__ void attend_split(const AttnParams& p, WaveState<D>& ws, int b, int hk, const Parts& parts, int t_begin,
-                             int t_end, int L, int64_t seq_row, int* next_item) {
+                             int stride, int ntiles, int t_end, int L, int64_t seq_row, int* next_item) {
   using TileT = typename TileOf<D, FP8>::type;
   using LoaderT = Loader<D, LAYOUT, FP8>;
   constexpr int KB = D / 32;
@@ -472,10 +474,10 @@ __device__ void attend_split(const AttnParams& p, WaveState<D>& ws, int b, int h
 #pragma unroll
   for (int n = 0; n < NT; ++n) acc[n] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  const int ntiles = (t_end - t_begin + 31) >> 5;
   // Fused append: the wave that owns the tile of token L - 1 stores its rows
   // first (not when the length was clamped: that row is not the new token's).
-  if (p.new_k != nullptr && t_end == L && L > 0 && w == (ntiles - 1) % kWaves && p.ctx_lens[b] == L) {
+  if (p.new_k != nullptr && L > 0 && t_begin + stride * (ntiles - 1) == ((L - 1) & ~31) &&
+      w == (ntiles - 1) % kWaves && p.ctx_lens[b] == L) {
     int64_t row;
     if constexpr (LAYOUT == Layout::kContig) {
       row = (seq_row + static_cast<int64_t>(L - 1)) * p.stride_token;
@@ -490,8 +492,9 @@ __device__ void attend_split(const AttnParams& p, WaveState<D>& ws, int b, int h
   // the compiler waits for exactly the older tile's loads.
   if (w < ntiles) {
     const int last = (ntiles - 1 - w) / kWaves;  // the wave's tiles 0 .. last
-    ld.t_first = t_begin + 32 * w;
-    auto token = [&](int n) { return ld.t_first + 32 * kWaves * n; };
+    ld.t_first = t_begin + stride * w;
+    ld.t_step = stride * kWaves;
+    auto token = [&](int n) { return ld.t_first + ld.t_step * n; };
     TileT A, B;
     ld.first_entries();
     ld.load(A, 0, token(0), false);
@@ -584,9 +587,26 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(const AttnPara
   const int chunk = p.ranges > 0 ? 32 * range_tiles(p, tiles_of(L)) : p.chunk;
   const EvenParts parts(p, b, hk, j, L, chunk);
   if (j >= parts.count) return;
-  const int t0 = j * chunk;
   __shared__ WaveState<D> ws;
-  attend_split<D, LAYOUT, FP8>(p, ws, b, hk, parts, t0, t0 + min(L - t0, chunk), L, seq_row, nullptr);
+  int t0 = j * chunk, stride = 32, t_end = t0 + min(L - t0, chunk), ntiles = (t_end - t0 + 31) >> 5;
+  if (p.ranges > 0) {
+    // Split j of n takes the tiles j, j + n, ... (a call with ranges has fewer
+    // than 2^23), not a run of them: the workgroups then read one moving window
+    // of the cache, where runs of a power of two of tokens start whole MiB
+    // apart (us per call, runs / strided, contiguous: 32768 tokens FP8 16.9 /
+    // 15.9 eager, 18.6 / 17.5 with cold caches, bf16 25.1 / 25.0 and 27.8 /
+    // 27.2; 6001, 20000 and 100001 within 0.7%). Pages lie scattered anyway
+    // and run 0-0.9% slower; they keep the same splits, so that a paged call
+    // returns the contiguous call's bits.
+    const int n = parts.count;
+    t0 = 32 * j;
+    stride = 32 * n;
+    t_end = L;
+    ntiles = L > 0 ? uniform_i32(static_cast<int>(div_small(tiles_of(L) - j + n - 1, n,
+                                                            __builtin_amdgcn_rcpf(static_cast<float>(n)))))
+                   : 0;
+  }
+  attend_split<D, LAYOUT, FP8>(p, ws, b, hk, parts, t0, stride, ntiles, t_end, L, seq_row, nullptr);
 }
 
 // In-place prefix sum by one wave: a[i + 1] (counts of sequences 0..n-1)
@@ -655,9 +675,9 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_queue_kernel(const At
     int L;
     int64_t seq_row;
     load_sequence<LAYOUT>(p, b, L, seq_row);
-    const int t0 = j * p.chunk;
-    attend_split<D, LAYOUT, FP8>(p, ws, b, hk, EvenParts(p, b, hk, j, L, p.chunk), t0, t0 + min(L - t0, p.chunk), L, seq_row,
-                                 queued ? &sm_next : nullptr);
+    const int t0 = j * p.chunk, t_end = t0 + min(L - t0, p.chunk);
+    attend_split<D, LAYOUT, FP8>(p, ws, b, hk, EvenParts(p, b, hk, j, L, p.chunk), t0, 32, (t_end - t0 + 31) >> 5, t_end, L,
+                                 seq_row, queued ? &sm_next : nullptr);
     __syncthreads();
     item = queued ? sm_next : total;
     __syncthreads();
@@ -750,8 +770,9 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_balanced_kernel(const
     if (piece_end > begin) {
       const int r0 = uniform_i32(static_cast<int>(div_small(begin, per, rper)));
       const int r1 = uniform_i32(static_cast<int>(div_small(end - 1, per, rper)));
-      attend_split<D, LAYOUT, FP8>(p, ws, b, hk, RangeParts(p, hk, r, r0, r1), 32 * max(cur - begin, 0),
-                                   min(L, 32 * (piece_end - begin)), L, seq_row, nullptr);
+      const int t0 = 32 * max(cur - begin, 0), t_end = min(L, 32 * (piece_end - begin));
+      attend_split<D, LAYOUT, FP8>(p, ws, b, hk, RangeParts(p, hk, r, r0, r1), t0, 32, (t_end - t0 + 31) >> 5, t_end, L, seq_row,
+                                   nullptr);
     }
     cur = piece_end;
     if (cur >= stop) return;

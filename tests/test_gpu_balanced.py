@@ -97,3 +97,29 @@ def test_balanced_fused_append(base, ps):
         out_b, _ = op.append_forward(b.q, tk, tv, b.k, b.v, b.seq_start, b.ctx_lens, spec.max_ctx_len)
     torch.cuda.synchronize()
     assert torch.equal(a.k, b.k) and torch.equal(a.v, b.v) and torch.equal(out_a, out_b)
+
+
+@pytest.mark.parametrize("base,ps", [(2, 0), (4, 16), (4, 1), (6, 0), (7, 64)])
+@pytest.mark.parametrize("length", [1, 31, 32, 33, 64, 65, 257, 2049, 6001])
+def test_one_sequence_in_strided_tiles(base, ps, length):
+    """One sequence: every split takes every n-th tile; the last tile, whichever split and wave has it, is partial and
+    takes the fused append's row."""
+    import torch
+
+    spec = _spec(base, [length], 8192, ps)
+    w = generate(spec, spare_pages=2, poison=True) if ps else generate(spec, gap_rows=5, poison=True)
+    nk, nv = draw_new_rows(spec, seed=540 + length)
+    tk, tv = to_torch(nk, spec.dtype, "cuda:0"), to_torch(nv, spec.dtype, "cuda:0")
+    a, op = DeviceWorkload(w), make_op(spec)
+    say(f"strided tiles: {length} tokens, {spec.dtype}, page {ps}")
+    ro, rl = da.reference(w)
+    check(*run(a, op), ro, rl, spec.dtype, f"{length} tokens")
+    b = DeviceWorkload(w)
+    where_a, where_b = (a.block_table, b.block_table) if ps else (a.seq_start, b.seq_start)
+    (op.append_paged if ps else op.append)(tk, tv, a.k, a.v, where_a, a.ctx_lens, spec.max_ctx_len)
+    out_a, _ = (op.forward_paged if ps else op.forward)(a.q, a.k, a.v, where_a, a.ctx_lens, spec.max_ctx_len)
+    fused = op.append_forward_paged if ps else op.append_forward
+    out_b, _ = fused(b.q, tk, tv, b.k, b.v, where_b, b.ctx_lens, spec.max_ctx_len)
+    torch.cuda.synchronize()
+    same = lambda x, y: torch.equal(x.view(torch.uint8), y.view(torch.uint8))  # noqa: E731 (NaN poison compares as bytes)
+    assert same(a.k, b.k) and same(a.v, b.v) and torch.equal(out_a, out_b)
