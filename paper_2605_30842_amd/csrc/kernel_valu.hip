@@ -5,10 +5,18 @@
 // cover one K/V row with one 16-byte load each (VEC elements), so a load
 // instruction reads RPL = 64 / LPR whole rows; a tile is U such loads per
 // lane (RPL * U tokens). Each lane computes its slice of the G dot products,
-// the slices are summed across the LPR lanes of the row with xor-shuffles,
-// and every lane then runs the online softmax of its row slot and
-// accumulates weight * V over its own head_dim slice. The row slots of a wave
-// are merged by log-sum-exp at the end.
+// the slices are summed across the LPR lanes of the row, and every lane then
+// runs the online softmax of its row slot and accumulates weight * V over its
+// own head_dim slice. The row slots of a wave are merged by log-sum-exp at
+// the end.
+//
+// Short calls are a chain of latencies, long ones are bound by the rate of the
+// sums: a tile takes U G log2(LPR) of them per lane. So lanes are joined by
+// data-parallel operands and row swaps of the vector unit, not by shuffles
+// through LDS, the first tile is requested before Q is waited for, and the
+// next tile while one is computed (where that pays). us, before -> after, f32:
+// 8 x 16384 tokens G = 8 268 -> 200, G = 4 in 16-token pages 244 -> 212; 3 x
+// 9000 G = 16 106 -> 56; 4 x 8000 G = 4, D = 64 35.5 -> 32.5.
 #include "attn_common.h"
 
 namespace comem {
@@ -39,6 +47,71 @@ struct Elem<Bf16> {
   }
 };
 
+template <int CTRL>
+__device__ inline float dpp(float x) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0, static_cast<int>(__float_as_uint(x)), CTRL, 0xf, 0xf, true));
+}
+
+// The values of the lanes O apart (bit O of the lane clear, set); for O = 8
+// the lane's own comes first.
+template <int O>
+__device__ inline void lane_pair(float x, float& x0, float& x1) {
+  const uint32_t u = __float_as_uint(x);
+  if constexpr (O == 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    x0 = __uint_as_float(r[0]);
+    x1 = __uint_as_float(r[1]);
+  } else if constexpr (O == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    x0 = __uint_as_float(r[0]);
+    x1 = __uint_as_float(r[1]);
+  } else {
+    x0 = x;
+    x1 = __shfl_xor(x, O);
+  }
+}
+
+// Sum over the LPR lanes of a row, in each of them: pairs and quads by quad
+// permutation (lane ^ 1, lane ^ 2), then mirrored halves of 8 and 16 lanes,
+// whose quads (halves) already hold one value.
+template <int LPR>
+__device__ inline float row_sum(float a) {
+  a += dpp<0xb1>(a);
+  a += dpp<0x4e>(a);
+  if constexpr (LPR >= 8) a += dpp<0x141>(a);
+  if constexpr (LPR >= 16) a += dpp<0x140>(a);
+  if constexpr (LPR == 32) {
+    float x0, x1;
+    lane_pair<16>(a, x0, x1);
+    a = x0 + x1;
+  }
+  return a;
+}
+
+// Merge the softmax states of the lanes O, 2 O, ... 32 apart.
+template <int O, int G, int VEC>
+__device__ inline void merge_slots(float (&m)[G], float (&l)[G], float (&acc)[G][VEC]) {
+  if constexpr (O < 64) {
+#pragma unroll
+    for (int h = 0; h < G; ++h) {
+      float m0, m1, x0, x1;
+      lane_pair<O>(m[h], m0, m1);
+      const float M = fmaxf(m0, m1);
+      const float a0 = M == -INFINITY ? 0.f : fast_exp2(m0 - M);
+      const float a1 = M == -INFINITY ? 0.f : fast_exp2(m1 - M);
+      lane_pair<O>(l[h], x0, x1);
+      l[h] = x0 * a0 + x1 * a1;
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) {
+        lane_pair<O>(acc[h][e], x0, x1);
+        acc[h][e] = x0 * a0 + x1 * a1;
+      }
+      m[h] = M;
+    }
+    merge_slots<2 * O, G, VEC>(m, l, acc);
+  }
+}
+
 template <typename T, int D, int G, bool PAGED>
 __global__ __launch_bounds__(kThreads) void decode_valu_kernel(const AttnParams p) {
   constexpr int VEC = Elem<T>::kVec;
@@ -47,8 +120,16 @@ __global__ __launch_bounds__(kThreads) void decode_valu_kernel(const AttnParams 
   constexpr int RPL = 64 / LPR;   // rows per load instruction
   constexpr int U = 4;            // loads per lane per tile
   constexpr int TT = RPL * U;     // tokens per tile
+  // A second tile in registers: with many heads it does not fit. With one or
+  // two, calls are bound by HBM and every tile is requested when it is due (8 x
+  // 16384 tokens, G = 1: 151.8 us, 155.2 with tiles ahead; 150.1 before).
+  constexpr bool kEarly = G >= 4;  // the first tile before Q, later ones as soon as the last is done
+  constexpr bool kAhead = kEarly && G * VEC <= 32;
   const int j = blockIdx.x, hk = blockIdx.y, b = blockIdx.z;
-  const int L = checked_len(p.ctx_lens[b], p.max_ctx, p.errors);
+  int L = p.ctx_lens[b];
+  int64_t seq0 = PAGED ? 0 : p.seq_start[b];
+  asm volatile("" : "+s"(L), "+s"(seq0));  // one round trip for both
+  L = checked_len(L, p.max_ctx, p.errors);
   const EvenParts parts(p, b, hk, j, L, p.chunk);
   if (j >= parts.count) return;
   const int t_begin = j * p.chunk;
@@ -58,20 +139,14 @@ __global__ __launch_bounds__(kThreads) void decode_valu_kernel(const AttnParams 
 
   __shared__ WaveState<D> ws;
 
-  float qf[G][VEC];
+  u32x4 qraw[G];
   {
     const char* q0 = p.q + (static_cast<int64_t>(b) * p.num_q_heads + hk * G) * D * EB;
 #pragma unroll
-    for (int h = 0; h < G; ++h) {
-      const u32x4 raw = *reinterpret_cast<const u32x4*>(q0 + (h * D + ds * VEC) * EB);
-      Elem<T>::widen(raw, qf[h]);
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) qf[h][e] *= p.scale_log2;
-    }
+    for (int h = 0; h < G; ++h) qraw[h] = *reinterpret_cast<const u32x4*>(q0 + (h * D + ds * VEC) * EB);
   }
   const char* kb = p.k + hk * p.stride_head;
   const char* vb = p.v + hk * p.stride_head;
-  const int64_t seq0 = PAGED ? 0 : p.seq_start[b];
 
   float m[G], l[G], acc[G][VEC];
 #pragma unroll
@@ -82,7 +157,6 @@ __global__ __launch_bounds__(kThreads) void decode_valu_kernel(const AttnParams 
     for (int e = 0; e < VEC; ++e) acc[h][e] = 0.f;
   }
 
-  const int ntok = t_end - t_begin;
   // Fused append: the wave whose tile holds token L - 1 (and every clamped
   // read of that row) stores the new rows first (not when the length was
   // clamped: that row is not the new token's).
@@ -96,14 +170,35 @@ __global__ __launch_bounds__(kThreads) void decode_valu_kernel(const AttnParams 
     }
     store_new_token(p, b, hk, row, D * EB / 16, lane);
   }
-  for (int base = t_begin + w * TT; base < t_begin + ntok; base += kWaves * TT) {
-    u32x4 kr[U], vr[U];
+  u32x4 kr[U], vr[U];
+  auto request = [&](int base, u32x4 (&k)[U], u32x4 (&v)[U]) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int t = min(base + u * RPL + rho, t_end - 1);
       const int64_t off = row_offset<PAGED>(p, b, seq0, t) + ds * 16;
-      kr[u] = *reinterpret_cast<const u32x4*>(kb + off);
-      vr[u] = *reinterpret_cast<const u32x4*>(vb + off);
+      k[u] = *reinterpret_cast<const u32x4*>(kb + off);
+      v[u] = *reinterpret_cast<const u32x4*>(vb + off);
+    }
+  };
+  int base = t_begin + w * TT;
+  if constexpr (kEarly) {
+    if (base < t_end) request(base, kr, vr);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  float qf[G][VEC];
+#pragma unroll
+  for (int h = 0; h < G; ++h) {
+    Elem<T>::widen(qraw[h], qf[h]);
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) qf[h][e] *= p.scale_log2;
+  }
+  while (base < t_end) {
+    const int next = base + kWaves * TT;
+    u32x4 kn[U], vn[U];
+    if constexpr (!kEarly) request(base, kr, vr);
+    if constexpr (kAhead) {
+      if (next < t_end) request(next, kn, vn);
+      __builtin_amdgcn_sched_barrier(0);
     }
     float s[U][G];
 #pragma unroll
@@ -115,8 +210,7 @@ __global__ __launch_bounds__(kThreads) void decode_valu_kernel(const AttnParams 
         float a = 0.f;
 #pragma unroll
         for (int e = 0; e < VEC; ++e) a += qf[h][e] * kf[e];
-#pragma unroll
-        for (int o = LPR / 2; o >= 1; o >>= 1) a += __shfl_xor(a, o);
+        a = row_sum<LPR>(a);
         s[u][h] = (base + u * RPL + rho < t_end) ? a : -INFINITY;
       }
     }
@@ -143,27 +237,20 @@ __global__ __launch_bounds__(kThreads) void decode_valu_kernel(const AttnParams 
       }
       m[h] = m_new;
     }
+    base = next;
+    if constexpr (kAhead) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        kr[u] = kn[u];
+        vr[u] = vn[u];
+      }
+    } else if constexpr (kEarly) {
+      if (base < t_end) request(base, kr, vr);
+    }
   }
 
   // Merge the RPL row slots of the wave (lanes that share ds).
-#pragma unroll
-  for (int o = LPR; o < 64; o <<= 1) {
-#pragma unroll
-    for (int h = 0; h < G; ++h) {
-      const float mo = __shfl_xor(m[h], o);
-      const float lo = __shfl_xor(l[h], o);
-      const float M = fmaxf(m[h], mo);
-      const float a = M == -INFINITY ? 0.f : fast_exp2(m[h] - M);
-      const float ao = M == -INFINITY ? 0.f : fast_exp2(mo - M);
-      l[h] = l[h] * a + lo * ao;
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) {
-        const float xo = __shfl_xor(acc[h][e], o);
-        acc[h][e] = acc[h][e] * a + xo * ao;
-      }
-      m[h] = M;
-    }
-  }
+  merge_slots<LPR, G, VEC>(m, l, acc);
   if (rho == 0) {
 #pragma unroll
     for (int h = 0; h < G; ++h) {
