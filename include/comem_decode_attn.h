@@ -16,7 +16,10 @@
  *     out   = sum_t softmax(s)_t * V_b[t, h / G, :]
  *     lse   = ln sum_t exp(s_t)
  *
- * L_b = 0 gives out = 0 and lse = -inf. The agent's full history and the
+ * L_b = 0 gives out = 0 and lse = -inf. A score of -inf has weight 0 (a
+ * context of nothing else is like an empty one); a NaN in q or K makes out and
+ * lse of the query heads that see it NaN, and an infinity in V makes the
+ * outputs it reaches infinite or NaN. The agent's full history and the
  * memory model's compressed context (summary plus recent buffer, Sec. 3.2)
  * are both just a shorter or longer cache, so one API serves both.
  *

@@ -29,6 +29,10 @@ constexpr int kMaxGroup = 16;       // largest GQA group handled in one workgrou
 // bytes a token and head, or of 256 and less).
 constexpr int kPieceTiles = 8, kPieceTilesLight = 12;
 constexpr float kLn2 = 0.69314718055994530942f;
+// Running maximum before any score: finite, so that a score of -inf (and a
+// tile or a split of nothing else) gets weight 0 and the difference of two
+// maxima is never NaN.
+constexpr float kLowest = -3.402823466e+38f;
 
 // Kernel arguments (passed by value). Offsets and strides are in bytes.
 struct AttnParams {
@@ -93,7 +97,7 @@ __device__ inline int32_t checked_page(int32_t page, int64_t num_pages, uint32_t
 // Per-wave partial state handed from the token loop to the finalize step.
 template <int D>
 struct WaveState {
-  float m[kWaves][kMaxGroup];   // running max (log2 units), -inf if no token seen
+  float m[kWaves][kMaxGroup];   // running max (log2 units), kLowest if no token seen
   float l[kWaves][kMaxGroup];   // sum of exp2(x - m)
   alignas(16) float o[kWaves][kMaxGroup][D + 4];  // sum of exp2(x - m) * v (rows 4 banks apart)
 };
@@ -335,7 +339,9 @@ __device__ void finalize_split(const AttnParams& p, const WaveState<D>& ws, int 
       const float4 o = *reinterpret_cast<const float4*>(&ws.o[w][h][d0]);
       st.add(ws.m[w][h], ws.l[w][h], o);  // wave sums are unnormalised: weight 2^m, sum l
     }
-    const bool live = st.wsum > 0.f;
+    // A sum of 0 is a split without a token (or of scores of -inf only). One of
+    // NaN (a NaN in q or K) stays NaN here and through the merge.
+    const bool live = st.wsum != 0.f;
     const float inv = live ? 1.f / st.wsum : 0.f;
     const float4 on = make_float4(st.acc.x * inv, st.acc.y * inv, st.acc.z * inv, st.acc.w * inv);
     const float lse2 = live ? st.m + log2f(st.wsum) : -INFINITY;
@@ -394,7 +400,7 @@ __device__ void finalize_split(const AttnParams& p, const WaveState<D>& ws, int 
       acc = st.acc;
     }
     if (sub == 0) {
-      const float inv = p.out_scale / wsum;
+      const float inv = wsum != 0.f ? p.out_scale / wsum : 0.f;  // 0: no split has a token with a weight
       *reinterpret_cast<float4*>(out + slot * 4) = make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
       if ((slot & ((1 << kLogRow) - 1)) == 0 && p.lse != nullptr) p.lse[head0 + h] = (m + log2f(wsum)) * kLn2;
     }

@@ -346,7 +346,6 @@ __device__ inline void compute_tile(const Tile<D>& T, int t0, int t_end, int g,
       x[4 * s + r] = v;
       mt = fmaxf(mt, v);
     }
-  // Every tile holds at least one valid token, so the new maximum is finite.
   const float m_new = fmaxf(m_run, across_groups(mt, Max{}));
   if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
     const float alpha = fast_exp2(m_run - m_new);
@@ -469,7 +468,7 @@ __device__ void attend_split(const AttnParams& p, WaveState<D>& ws, int b, int h
     }
   }
 
-  float m_run = -INFINITY, l_run = 0.f;
+  float m_run = kLowest, l_run = 0.f;
   f32x4 acc[NT];
 #pragma unroll
   for (int n = 0; n < NT; ++n) acc[n] = f32x4{0.f, 0.f, 0.f, 0.f};

@@ -97,8 +97,8 @@ __device__ inline void merge_slots(float (&m)[G], float (&l)[G], float (&acc)[G]
       float m0, m1, x0, x1;
       lane_pair<O>(m[h], m0, m1);
       const float M = fmaxf(m0, m1);
-      const float a0 = M == -INFINITY ? 0.f : fast_exp2(m0 - M);
-      const float a1 = M == -INFINITY ? 0.f : fast_exp2(m1 - M);
+      const float a0 = fast_exp2(m0 - M);
+      const float a1 = fast_exp2(m1 - M);
       lane_pair<O>(l[h], x0, x1);
       l[h] = x0 * a0 + x1 * a1;
 #pragma unroll
@@ -151,7 +151,7 @@ __global__ __launch_bounds__(kThreads) void decode_valu_kernel(const AttnParams 
   float m[G], l[G], acc[G][VEC];
 #pragma unroll
   for (int h = 0; h < G; ++h) {
-    m[h] = -INFINITY;
+    m[h] = kLowest;
     l[h] = 0.f;
 #pragma unroll
     for (int e = 0; e < VEC; ++e) acc[h][e] = 0.f;
@@ -217,25 +217,25 @@ __global__ __launch_bounds__(kThreads) void decode_valu_kernel(const AttnParams 
     float vf[U][VEC];
 #pragma unroll
     for (int u = 0; u < U; ++u) Elem<T>::widen(vr[u], vf[u]);
+    if (base + rho < t_end) {  // else the tile has no token for this row slot
 #pragma unroll
-    for (int h = 0; h < G; ++h) {
-      float mt = s[0][h];
+      for (int h = 0; h < G; ++h) {
+        float m_new = m[h];
 #pragma unroll
-      for (int u = 1; u < U; ++u) mt = fmaxf(mt, s[u][h]);
-      const float m_new = fmaxf(m[h], mt);
-      if (m_new == -INFINITY) continue;  // no valid token in this row slot yet
-      const float alpha = fast_exp2(m[h] - m_new);
-      l[h] *= alpha;
+        for (int u = 0; u < U; ++u) m_new = fmaxf(m_new, s[u][h]);
+        const float alpha = fast_exp2(m[h] - m_new);
+        l[h] *= alpha;
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) acc[h][e] *= alpha;
+        for (int e = 0; e < VEC; ++e) acc[h][e] *= alpha;
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const float pu = fast_exp2(s[u][h] - m_new);
-        l[h] += pu;
+        for (int u = 0; u < U; ++u) {
+          const float pu = fast_exp2(s[u][h] - m_new);
+          l[h] += pu;
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) acc[h][e] += pu * vf[u][e];
+          for (int e = 0; e < VEC; ++e) acc[h][e] += pu * vf[u][e];
+        }
+        m[h] = m_new;
       }
-      m[h] = m_new;
     }
     base = next;
     if constexpr (kAhead) {
