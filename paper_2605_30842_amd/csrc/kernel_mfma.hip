@@ -184,6 +184,10 @@ struct Loader {
   // of the wave's tile 32 i + l / 2, that of `next` the entries of the 32
   // tiles after those. Smaller pages: lane l < 32 of `now` holds the entry of
   // token l of the tile to be requested, `next` those of the tile after it.
+  // Entries are checked as they become `now`, once each. (Checked for every
+  // row of the 10 a lane reads, with a branch to the error word: 1-token pages,
+  // 8 KV heads, us before / after: 32768 tokens bf16 33.5 / 32.2, FP8 22.9 /
+  // 17.9; 16 x 400-4000 FP8 30.2 / 23.8; 6 x 1200-12000 bf16 44.6 / 41.9.)
   int32_t now, next;
 
   // An entry outside the pool reads page 0.
@@ -205,7 +209,7 @@ struct Loader {
       now = in_pool(entries(0));
       next = entries(32);
     } else if constexpr (LAYOUT == Layout::kPagedFine) {
-      now = entries(0);
+      now = in_pool(entries(0));
       next = entries(1);
     }
   }
@@ -222,7 +226,7 @@ struct Loader {
         next = entries(n + 32);
       }
     } else if constexpr (LAYOUT == Layout::kPagedFine) {
-      now = next;
+      now = in_pool(next);
       next = entries(n + 1);
     }
   }
@@ -294,8 +298,7 @@ struct Loader {
   // Small pages: byte offset of row i of the tile at t0, clamped to the last valid one.
   __device__ int64_t lane_row(int t0, int i) const {
     const int ic = min(i, t_end - 1 - t0);
-    return static_cast<int64_t>(in_pool(__shfl(now, ic))) * stride_page +
-           tokens((t0 + ic) & page_mask);
+    return static_cast<int64_t>(__shfl(now, ic)) * stride_page + tokens((t0 + ic) & page_mask);
   }
 };
 
