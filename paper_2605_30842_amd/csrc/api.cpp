@@ -146,18 +146,33 @@ int64_t long_chunk(const comem_decode_attn_plan& p, int64_t batch, int64_t L) {
 // Long calls of several sequences take the balanced form, short ones one
 // workgroup per split. The balanced kernel starts 1-2 us later, and a range
 // pays for every piece it holds; its equal shares win that back once ranges
-// are long. Swept over 2-128 sequences, 2-8 KV heads, bf16 and FP8, head_dim
-// 64 and 128, lengths from 0.15, 0.5 and 1 of the bound up (best splits /
-// balanced): at 900-1000 tokens of bound per range and sequence 0.87-1.05, at
-// 1365 0.94-1.27, at 1638-1820 0.96-1.27, from 2700 0.97-1.35. With a pair of
-// sequence and head for every compute unit, unsplit sequences end evenly
-// enough by themselves: at 1365 0.88-1.08, at 1638 (512-byte tokens)
-// 1.00-1.08, and lighter tokens, whose pieces cost relatively more, at 1638
-// 0.92-1.04, at 2048 0.96-1.09.
+// are long.
+//
+// With fewer pairs of sequence and head than compute units, swept over 2-128
+// sequences, 2-8 KV heads, bf16 and FP8, head_dim 64 and 128, lengths from
+// 0.15, 0.5 and 1 of the bound up (best splits / balanced): at 900-1000 tokens
+// of bound per range and sequence 0.87-1.05, at 1365 0.94-1.27, from 2700
+// 0.97-1.35.
+//
+// With a pair for every unit, short calls run whole sequences, and a call then
+// takes as long as its longest one on one unit (0.01 us a token) unless the
+// others keep the units busy as long: with few sequences per range the line
+// rises with them. With many, a range's pieces even out by themselves and the
+// line falls towards the length at which whole sequences of about equal length
+// stop being faster. Swept over 12-512 sequences, 2-32 KV heads, bounds 1100
+// to 8192, lengths equal, uniform from 0.1 or 0.5 of the bound, and one or a
+// sixteenth of them at the bound and the others at 0.02-0.1 of it (us, whole
+// / balanced, equal lengths; uniform from 0.1; one long and the others a
+// tenth): 32 x 8 heads 1100 tokens 25.0 / 25.8; 18.8 / 20.1; 16.8 / 13.0, 2000
+// 39.9 / 41.4; 30.7 / 30.6; 26.0 / 14.9, 3100 64.1 / 65.2; 43.4 / 38.8; 37.6 /
+// 17.0. 128 x 8 2048 168 / 166; 110 / 105; 32.1 / 32.9, 3100 244 / 246; 163 /
+// 152; 52.6 / 45.5. 256 x 8 2048 326 / 324; 202 / 197; 39 / 55, 3100 482 / 485;
+// 298 / 282; 64 / 80. Light tokens cost a range's pieces relatively more.
 bool long_call(const comem_decode_attn_plan& p, int64_t batch, int64_t L) {
+  const int64_t ranges = max_ranges(p);
+  if (batch * p.cfg.num_kv_heads < p.num_cus) return batch * L >= 1200 * (ranges + batch);
   const bool light = p.cfg.head_dim * elem_bytes(p.cfg) <= 128;
-  const int64_t tokens = batch * p.cfg.num_kv_heads < p.num_cus ? 1200 : (light ? 2048 : 1600);
-  return batch * L >= tokens * (max_ranges(p) + batch);
+  return L >= (light ? 1500 : 1000) + 260 * batch / ranges || batch * L >= (light ? 2048 : 1600) * (ranges + batch);
 }
 
 // Tokens per split of a short call: one split per compute unit, none shorter

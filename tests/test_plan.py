@@ -24,7 +24,9 @@ def test_spread_tickets_fit_wherever_dense_ones_did(max_batch):
     (1, 8192, 256),   # one split per compute unit
     (6, 4096, 832),   # 5 splits for each of 48 (sequence, head) pairs
     (4, 16384, 1024),  # never above 1024 while some unit is free
-    (32, 3000, 3008),  # the pairs fill the chip: no split
+    (32, 1200, 1216),  # the pairs fill the chip: no split
+    (32, 3000, 1024),  # one long sequence among short ones would run alone: ranges (splits without the workspace)
+    (96, 1700, 1728),  # ... but not with several sequences to each range
 ])
 def test_short_calls_plan_one_split_per_compute_unit(batch, L, chunk):
     p, ws = B.comem_decode_attn_init(_cfg(max_batch=batch, max_ctx_len=L), B.NO_DEVICE)
