@@ -100,13 +100,23 @@ int64_t mfma_page_cap(int64_t page_size) {
   return std::max<int64_t>(32, (kMaxSplitPages - 2) * page_size / 32 * 32);
 }
 
-// Ranges of the balanced form (decode_mfma_balanced_kernel): one workgroup
-// per compute unit, `ranges` for each KV head. Above 32 KV heads that would
-// leave up to half the units idle, so two per unit there; one range (more
-// heads than workgroups) means no split at all.
+// Ranges of the balanced form (decode_mfma_balanced_kernel), for each KV head:
+// one workgroup per compute unit; two where one would leave more than 15% of
+// the units idle (43 heads: 5 ranges on 215 of 256).
 int64_t max_ranges(const comem_decode_attn_plan& p) {
-  const int64_t wgs = p.num_cus * (p.cfg.num_kv_heads > 32 ? 2 : 1);
-  return std::max<int64_t>(1, wgs / p.cfg.num_kv_heads);
+  const int64_t heads = p.cfg.num_kv_heads, one = p.num_cus / heads;
+  return 20 * one * heads >= 17 * p.num_cus ? one : std::max<int64_t>(1, 2 * p.num_cus / heads);
+}
+
+// With many KV heads a head has so few ranges that they can't even out: the
+// unequal sums of a unit's or an XCD's neighbours show. us, splits / ranges, G
+// = 1: 4 x 8192 tokens, 40 heads D = 128 122 / 115, 64 178 / 172, 80 225 /
+// 247, D = 64 96 139 / 154, 160 233 / 307; one sequence of 8192, 40 heads D =
+// 128 38.5 / 31.3, 96 70.8 / 70.7, 128 94 / 87, 300 of 4096 D = 64 59 / 70,
+// FP8 160 of 8192 72 / 80.
+bool can_balance(const comem_decode_attn_plan& p, int64_t batch) {
+  return uses_mfma(p) && p.cfg.variant != COMEM_VARIANT_MFMA_GRID && p.cfg.chunk_tokens == 0 &&
+         batch <= comem::mfma_max_queue_batch() && p.cfg.num_kv_heads <= (batch == 1 ? 128 : 64);
 }
 
 // Workspace bytes of the balanced form past the tickets: two partial-result
@@ -261,13 +271,11 @@ bool uses_queue(const comem_decode_attn_plan& p, int64_t batch, const void* work
          workspace != nullptr && ws_bytes >= p.ticket_bytes;
 }
 
-// The balanced form of the matrix-core kernel: planned splits, a workspace
-// for its partial results, and a token count its 24-bit arithmetic holds.
+// The balanced form of the matrix-core kernel needs a workspace for its partial
+// results and a token count that its 24-bit arithmetic holds.
 bool uses_balanced(const comem_decode_attn_plan& p, int64_t batch, int64_t max_ctx, const void* workspace,
                    size_t ws_bytes, size_t ticket_region) {
-  return uses_mfma(p) && p.cfg.variant != COMEM_VARIANT_MFMA_GRID && p.cfg.chunk_tokens == 0 &&
-         (batch == 1 || long_call(p, batch, max_ctx)) && batch <= comem::mfma_max_queue_batch() &&
-         workspace != nullptr && ws_bytes >= ticket_region + balanced_bytes(p) &&
+  return can_balance(p, batch) && (batch == 1 || long_call(p, batch, max_ctx)) && workspace != nullptr && ws_bytes >= ticket_region + balanced_bytes(p) &&
          batch * (ceil_div(max_ctx + 1, 32) + comem::kPieceTilesLight) < kMaxBalancedTiles;
 }
 
@@ -304,8 +312,13 @@ comem_status launch(const comem_decode_attn_plan& p, bool paged, comem::AttnPara
   const int64_t items = batch * p.cfg.num_kv_heads * splits;
   const int64_t resident = static_cast<int64_t>(kQueueWgsPerCu) * p.num_cus;
   // With no more (nominal) items than resident workgroups every item gets its
-  // own workgroup anyway, and the grid form saves the queue's prologue.
-  if (queue && items > resident && (p.cfg.chunk_tokens > 0 || long_call(p, batch, a.max_ctx))) {
+  // own workgroup anyway, and the grid form saves the queue's prologue; whole
+  // sequences (short calls with a pair for every compute unit) start without it
+  // too. Splits past the resident ones would wait in the grid for a unit of
+  // their own XCD (2 x 8192 tokens, 33 heads, FP8: 30.1 us, queued 25.7).
+  const bool whole = p.cfg.chunk_tokens == 0 && !long_call(p, batch, a.max_ctx) &&
+                     batch * p.cfg.num_kv_heads >= p.num_cus;
+  if (queue && items > resident && !whole) {
     comem::QueueKernelFn qfn = comem::select_mfma_queue_kernel(p.cfg.head_dim, paged, a.page_mask + 1, is_fp8(p.cfg));
     if (qfn == nullptr) return COMEM_ERR_UNSUPPORTED;
     dim3 grid(static_cast<unsigned>(items < resident ? items : resident));

@@ -47,6 +47,12 @@ CASES = {
     "5 heads, D 64": (2, _ragged(9, 9000, 10), 65536, 0, dict(num_q_heads=10, num_kv_heads=5, head_dim=64)),
     "G 16": (2, _ragged(9, 9000, 11), 65536, 0, dict(num_q_heads=32, num_kv_heads=2)),
     "40 heads": (2, _ragged(9, 2500, 12), 65536, 16, dict(num_q_heads=40, num_kv_heads=40, head_dim=64)),
+    "43 heads (two ranges a unit)": (2, _ragged(9, 2500, 13), 65536, 0, dict(num_q_heads=43, num_kv_heads=43, head_dim=64)),
+    "64 heads": (2, _ragged(5, 2500, 14), 65536, 0, dict(num_q_heads=64, num_kv_heads=64, head_dim=64)),
+    "65 heads (splits)": (2, _ragged(5, 2500, 15), 65536, 0, dict(num_q_heads=65, num_kv_heads=65, head_dim=64)),
+    "one long, 128 heads": (2, [4001], 4001, 0, dict(num_q_heads=128, num_kv_heads=128, head_dim=64)),
+    "one long, 129 heads (splits)": (2, [4001], 4001, 0, dict(num_q_heads=129, num_kv_heads=129, head_dim=64)),
+    "more splits than workgroups": (6, [8192, 3000], 8192, 0, dict(num_q_heads=66, num_kv_heads=66, head_dim=64)),
     "600 heads (no split)": (2, [700, 0, 33], 65536, 0, dict(num_q_heads=600, num_kv_heads=600, head_dim=64)),
 }
 
