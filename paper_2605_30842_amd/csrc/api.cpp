@@ -139,6 +139,20 @@ float split_coefficient(const comem_decode_attn_plan& p) {
   return m / (32.f * a);
 }
 
+// Most tokens of a sequence that are better left to one workgroup than shared
+// by n: a second part costs a ticket and a merge, about 3 us (5 with the 2048
+// output values of G = 16, D = 128), and n parts save (n - 1) / n of the time
+// per token. Swept over one sequence and 2-30, 1-8 KV heads, G = 1, 4 and 16,
+// contexts of 40 to 800 tokens (us, whole / split; one sequence of 8 heads, G =
+// 4): 512-byte tokens 100 tokens 5.5 / 6.5, 280 6.9 / 6.6, 430 8.0 / 6.8; FP8
+// 100 4.6 / 6.5, 430 6.4 / 6.7, 640 7.5 / 6.9; G = 16 430 8.7 / 8.6, FP8 640 7.8
+// / 8.7; in two parts (16 sequences) 640 12.7 / 13.0, FP8 640 9.1 / 9.9.
+int64_t whole_tokens(const comem_decode_attn_plan& p, int64_t n) {
+  if (n <= 1) return kMaxContext;
+  const int64_t tokens = p.cfg.head_dim * elem_bytes(p.cfg) <= 128 ? 440 : 280;
+  return (group_of(p.cfg) * p.cfg.head_dim >= 2048 ? 3 * tokens / 2 : tokens) * n / (n - 1);
+}
+
 // Tokens per split of a long call in the grid and work-queue forms, from the
 // host-side bounds (the device-side lengths are never read on the host). Splits of
 // 4096 tokens keep contexts of 128k and more at <= 32 splits; otherwise 2048
@@ -193,7 +207,9 @@ bool long_call(const comem_decode_attn_plan& p, int64_t batch, int64_t L) {
 int64_t short_chunk(const comem_decode_attn_plan& p, int64_t batch, int64_t L) {
   const int64_t pairs = batch * p.cfg.num_kv_heads;
   if (pairs >= p.num_cus) return ceil_div(L, 32) * 32;
-  const int64_t share = ceil_div(L, p.num_cus / pairs);
+  const int64_t parts = p.num_cus / pairs;
+  if (parts > 1 && L <= whole_tokens(p, parts)) return ceil_div(L, 32) * 32;
+  const int64_t share = ceil_div(L, parts);
   const double piece = 32.0 * std::sqrt(split_coefficient(p) * static_cast<double>(ceil_div(L, 32)));
   const int64_t chunk = std::max({kMinRangeTokens, share, static_cast<int64_t>(std::ceil(piece))});
   return std::min<int64_t>(1024, ceil_div(chunk, 32) * 32);
@@ -292,6 +308,7 @@ comem_status launch_balanced(const comem_decode_attn_plan& p, bool paged, comem:
     comem::KernelFn fn = comem::select_mfma_kernel(p.cfg.head_dim, paged, page, is_fp8(p.cfg));
     if (fn == nullptr) return COMEM_ERR_UNSUPPORTED;
     a.num_splits = a.ranges;
+    a.whole_tiles = static_cast<int32_t>(whole_tokens(p, max_ranges(p)) / 32);
     void* args[] = {&a};
     err = hipLaunchKernel(reinterpret_cast<const void*>(fn), dim3(ranges, heads), dim3(comem::kThreads), args, 0,
                           static_cast<hipStream_t>(stream));

@@ -57,6 +57,7 @@ struct AttnParams {
   int32_t num_splits;  // most splits of one sequence (the stride of the partial results)
   int32_t ranges;      // balanced form: equal ranges of the call's tokens, else 0
   float split_coef;    // balanced form: (shortest piece in 32-token tiles)^2 / tiles of the call
+  int32_t whole_tiles; // balanced form of one sequence: up to so many tiles are not split
   float scale_log2;    // scale * log2(e)
   uint32_t* tickets;   // [max_batch * Hkv] tickets 2^ticket_shift words apart, then 2 queue counters; zero between calls
   int32_t queue_slot;  // index of the queue counters in tickets

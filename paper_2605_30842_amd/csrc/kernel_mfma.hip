@@ -553,8 +553,10 @@ __device__ inline uint32_t div_small(uint32_t a, uint32_t d, float rd) {
 __device__ inline int tiles_of(int L) { return L > 0 ? (L + 31) >> 5 : 1; }
 
 // Tiles per range of a call of `total` tiles: an equal share of the ranges,
-// but no less than a piece should have (see decode_mfma_balanced_kernel).
+// but no less than a piece should have (see decode_mfma_balanced_kernel), and
+// one sequence of at most p.whole_tiles whole.
 __device__ inline int range_tiles(const AttnParams& p, int total) {
+  if (total <= p.whole_tiles) return total;
   const int share = static_cast<int>(
       div_small(total + p.ranges - 1, p.ranges, __builtin_amdgcn_rcpf(static_cast<float>(p.ranges))));
   const float piece = __builtin_ceilf(__builtin_amdgcn_sqrtf(p.split_coef * static_cast<float>(total)));

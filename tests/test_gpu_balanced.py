@@ -106,7 +106,7 @@ def test_balanced_fused_append(base, ps):
 
 
 @pytest.mark.parametrize("base,ps", [(2, 0), (4, 16), (4, 1), (6, 0), (7, 64)])
-@pytest.mark.parametrize("length", [1, 31, 32, 33, 64, 65, 257, 2049, 6001])
+@pytest.mark.parametrize("length", [1, 31, 32, 33, 64, 65, 257, 288, 289, 321, 448, 449, 641, 2049, 6001])
 def test_one_sequence_in_strided_tiles(base, ps, length):
     """One sequence: every split takes every n-th tile; the last tile, whichever split and wave has it, is partial and
     takes the fused append's row."""

@@ -20,6 +20,11 @@ def test_spread_tickets_fit_wherever_dense_ones_did(max_batch):
 
 
 @pytest.mark.parametrize("batch,L,chunk", [
+    (1, 100, 128),     # not worth a merge
+    (1, 289, 320),
+    (1, 290, 64),
+    (16, 560, 576),    # two parts of a sequence save half of it
+    (16, 561, 288),
     (1, 2048, 128),   # latency-bound: pieces worth their merge
     (1, 8192, 256),   # one split per compute unit
     (6, 4096, 832),   # 5 splits for each of 48 (sequence, head) pairs
