@@ -2,6 +2,8 @@
 // validation (before any HIP call) and launch of the prefill kernel.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cmath>
 #include <cstdint>
 #include <cstring>
 
@@ -68,24 +70,56 @@ size_t split_bytes(const comem_decode_attn_plan& p, int64_t items, int64_t split
   return align256(rows * 4) + rows * static_cast<size_t>(p.cfg.head_dim) * 4;
 }
 
-// Workgroups per query block. One workgroup runs on a compute unit (its K and
-// V tiles take 128 KB of LDS) and takes about 1.2 us per 64-key tile, so a
-// call of `items` workgroups takes ceil(items / units) rounds of its tiles,
-// and a few new tokens over a long prefix leave most units idle (300 tokens
-// over 24300, G = 4, 8 KV heads: 80 workgroups). With the keys of every block
-// shared by `splits` workgroups the rounds are shorter and end more evenly,
-// and the partial results go out and come back once (about 3 TB/s, and 6 us
-// for the second launch and its latency). The count with the least estimate
-// wins, among those that leave a split at least 8 tiles. Measured (us, one
-// workgroup per block / split, G = 4, 8 KV heads, D = 128): 300 tokens over
-// 24300 318 / 171 (3 splits), 128 over 24300 316 / 74 (8), 1100 over 32768 999
-// / 745 (5), 256 over 8000 122 / 56 (4), four of 100-300 over 8K-16K 223 /
-// 202; with one round and a little (1024 over 32768) or many rounds nothing is
-// gained and nothing split.
+// Estimated us of a call whose blocks' keys `splits` workgroups each share.
+// One workgroup runs on a compute unit (its K and V tiles take 128 KB of LDS).
+// A 64-key tile takes it 0.7 us on an idle GPU and 1.2 on a full one, whose
+// clock the power limits (head_dim 64: 0.66 and 0.8), its start and end 12 us
+// (9), and the partial results go out and come back once, at about 3 TB/s.
+// Unsplit blocks differ: each sees the keys up to its own last token, so the
+// units need the rounds of the largest blocks, or, where blocks are many and
+// small, an even share of all tiles and half of the difference between the
+// largest and the smallest block.
+double prefill_us(const comem_decode_attn_plan& p, int64_t pairs, int64_t blocks, int64_t max_ctx_len,
+                  int64_t splits) {
+  const double units = p.num_cus, block_tiles = comem::kPrefillRows / group_of(p.cfg) / 64.0;
+  const double items = static_cast<double>(pairs * blocks);
+  const double most = static_cast<double>(ceil_div(max_ctx_len, comem::kPrefillTileKeys));
+  const double least = std::max(1.0, most - block_tiles * static_cast<double>(blocks - 1));
+  const double even = items * (most + least) / 2 / units;
+  const double rounds = std::ceil(items * static_cast<double>(splits) / units);
+  double steps = rounds * std::ceil(most / static_cast<double>(splits));
+  if (splits == 1) {
+    // Round r's largest block is (r - 1) units / pairs blocks from the largest.
+    const double drop = block_tiles * units / static_cast<double>(pairs);
+    const double r = std::min(rounds, std::max(1.0, std::floor((most + drop) / (2 * drop))));
+    steps = std::max({most, r * (most - drop * (r - 1)), rounds * (most - drop * (rounds - 1)),
+                      even + (most - least) / 2});
+  }
+  const double load = std::min(1.0, even / steps);
+  const bool wide = p.cfg.head_dim == 128;
+  const double us = (wide ? 12 : 9) + (wide ? 0.7 + 0.5 * load : 0.66 + 0.14 * load) * steps;
+  return us + (splits > 1 ? 2 + 2 * static_cast<double>(split_bytes(p, pairs * blocks, splits)) / 3e6 : 0);
+}
+
+// Workgroups per query block. A few new tokens over a long prefix leave most
+// units idle (300 tokens over 24300, G = 4, 8 KV heads: 80 workgroups). With
+// the keys of every block shared by several workgroups the rounds are shorter
+// and end more evenly; the count with the shortest rounds is taken, of those
+// that leave a split at least 8 tiles, where the call is estimated to gain 5%.
+// Measured over 43 shapes and both head_dims, every split count forced in turn
+// (us, unsplit / taken; best where another count is): head_dim 128, 8 KV heads,
+// G = 4: 300 tokens over 24300 317 / 167 (3 splits), 32 311 / 38.6, 1100 over
+// 32768 1027 / 765 (5), 256 over 8000 113 / 57 (4), 500 over 4096 69 / 61; G =
+// 2: 700 over 12000, twice, stays unsplit (189; 198 in 4), 5000 uncached tokens
+// of 4 heads too (92; 106 in 2). head_dim 64: 300 over 24300 261 / 109, 1100
+// over 32768 727 / 491 (490), 500 over 4096 55 / 42, the 5000 stay at 67 (77 in
+// 2), the 700 take 128 (134 unsplit). With one round and a little, or many
+// rounds, nothing is gained and nothing split (1024 over 32768: 639; 650 in 2).
 int64_t plan_splits(const comem_decode_attn_plan& p, int64_t batch, int64_t max_q_len, int64_t max_ctx_len,
                     size_t bytes) {
   constexpr int64_t kMinTiles = 8, kMaxSplits = 64;
-  const int64_t items = batch * p.cfg.num_kv_heads * ceil_div(max_q_len, comem::kPrefillRows / group_of(p.cfg));
+  const int64_t pairs = batch * p.cfg.num_kv_heads;
+  const int64_t blocks = ceil_div(max_q_len, comem::kPrefillRows / group_of(p.cfg)), items = pairs * blocks;
   const int64_t tiles = ceil_div(max_ctx_len, comem::kPrefillTileKeys);
   if (items >= 8 * p.num_cus) return 1;  // rounds are many, the last one is a small part
   int64_t best = 1;
@@ -99,6 +133,8 @@ int64_t plan_splits(const comem_decode_attn_plan& p, int64_t batch, int64_t max_
       least = us;
     }
   }
+  if (best > 1 && prefill_us(p, pairs, blocks, max_ctx_len, best) > 0.95 * prefill_us(p, pairs, blocks, max_ctx_len, 1))
+    return 1;
   return best;
 }
 

@@ -86,3 +86,20 @@ def test_prefill_workspace_sizes():
             B.comem_prefill_attn_workspace(p, 9, 300, 24300)
     finally:
         B.comem_decode_attn_destroy(p)
+
+
+@pytest.mark.parametrize("hq,hkv,d,batch,m,L,splits", [
+    (8, 4, 128, 1, 5000, 5000, False),   # causal: the blocks see half the keys on average
+    (8, 4, 64, 1, 5000, 5000, False),
+    (16, 8, 128, 2, 700, 12000, False),  # one round at two thirds of the units
+    (16, 8, 64, 2, 700, 12000, True),    # ... whose shorter tiles a split evens out
+    (32, 8, 64, 1, 300, 24300, True),
+    (4, 4, 128, 1, 4000, 4000, True),    # causal, but half of the units idle
+])
+def test_prefill_splits_only_where_it_gains(hq, hkv, d, batch, m, L, splits):
+    cfg = _cfg(num_q_heads=hq, num_kv_heads=hkv, head_dim=d, max_batch=batch, max_ctx_len=L)
+    p, _ = B.comem_decode_attn_init(cfg, B.NO_DEVICE)
+    try:
+        assert (B.comem_prefill_attn_workspace(p, batch, m, L) > 0) == splits
+    finally:
+        B.comem_decode_attn_destroy(p)
