@@ -13,10 +13,12 @@
 // Short calls are a chain of latencies, long ones are bound by the rate of the
 // sums: a tile takes U G log2(LPR) of them per lane. So lanes are joined by
 // data-parallel operands and row swaps of the vector unit, not by shuffles
-// through LDS, the first tile is requested before Q is waited for, and the
-// next tile while one is computed (where that pays). us, before -> after, f32:
-// 8 x 16384 tokens G = 8 268 -> 200, G = 4 in 16-token pages 244 -> 212; 3 x
-// 9000 G = 16 106 -> 56; 4 x 8000 G = 4, D = 64 35.5 -> 32.5.
+// through LDS, and where that pays the first tile is requested before Q is
+// waited for, and the next tile while one is computed. us, with shuffles and
+// every tile requested when due -> now, f32, 8 x 8192 tokens, D = 128, 8 KV
+// heads (4 at G = 16), contiguous and in 16-token pages: G = 1 95.3 -> 95.6 and
+// 129 -> 114, G = 4 98.9 -> 95.4 and 132 -> 113, G = 8 150 -> 113 and 175 ->
+// 135, G = 16 219 -> 137 and 378 -> 173.
 #include "attn_common.h"
 
 namespace comem {
@@ -120,11 +122,29 @@ __global__ __launch_bounds__(kThreads) void decode_valu_kernel(const AttnParams 
   constexpr int RPL = 64 / LPR;   // rows per load instruction
   constexpr int U = 4;            // loads per lane per tile
   constexpr int TT = RPL * U;     // tokens per tile
-  // A second tile in registers: with many heads it does not fit. With one or
-  // two, calls are bound by HBM and every tile is requested when it is due (8 x
-  // 16384 tokens, G = 1: 151.8 us, 155.2 with tiles ahead; 150.1 before).
-  constexpr bool kEarly = G >= 4;  // the first tile before Q, later ones as soon as the last is done
-  constexpr bool kAhead = kEarly && G * VEC <= 32;
+  // kEarly: the first tile before Q, later ones as soon as the last is done;
+  // kAhead: the next tile while one is computed, where a second one fits the
+  // registers. Contiguous caches gain from neither unless a tile's sums take
+  // long (8 and 16 float32 heads); in pages a tile waits for its block-table
+  // entries first. us, when due / early / ahead (8 x 8192 tokens, 8 KV heads, 4
+  // at G = 16; D = 128, then 64). Contiguous: f32 G = 2 95.0 / 95.0 / 95.3 and
+  // 50.3 / 51.7 / 51.9, G = 4 95.1 / 99.2 / 98.6 and 50.3 / 54.5 / 54.6, G = 8
+  // 120 / 121 / 117 and 59.8 / 60.6 / 59.3, G = 16 140 / 143 / 130 and 74.5 /
+  // 72.9 / 68.5; bf16 G = 4 53.4 / 55.6 / 57.7 and 31.1 / 34.2 / 34.7, G = 8
+  // 77.7 / 79.2 / 97.8 and 46.0 / 47.9 / 58.2. 16-token pages: f32 G = 1 126 /
+  // 115 / 114, G = 2 128 / 117 / 114, G = 4 130 / 123 / 114, G = 8 147 / 149 /
+  // 147 and 76.5 / 75.1 / 72.9, G = 16 157 / 157 / 166 and 85.4 / 84.2 / 87.2;
+  // bf16 G = 4 74.0 / 71.2 / 65.6, G = 8 92 / 147 / 128, G = 16 129 / 130 / 159
+  // and 81.5 / 77.9 / 91.4.
+  constexpr bool kWide = VEC == 4;  // float32
+  constexpr bool kAhead = PAGED ? G <= 4 || (G == 8 && kWide) : G >= 8 && kWide;
+  constexpr bool kEarly = kAhead || (PAGED && G == 16);
+  // A row slot without a token of a tile has nothing to add for it: one branch
+  // around all heads, or one for each where a tile of bf16 heads fills the
+  // registers, which keeps the heads' sums from being scheduled together (G =
+  // 16 contiguous 123 and 74.8 us with one branch, 110 and 70.5 with one each;
+  // f32 G = 8 120 and 125, G = 16 140 and 157).
+  constexpr bool kPerHead = !kWide && (G == 16 || (G == 8 && !PAGED));
   const int j = blockIdx.x, hk = blockIdx.y, b = blockIdx.z;
   int L = p.ctx_lens[b];
   int64_t seq0 = PAGED ? 0 : p.seq_start[b];
@@ -211,31 +231,43 @@ __global__ __launch_bounds__(kThreads) void decode_valu_kernel(const AttnParams 
 #pragma unroll
         for (int e = 0; e < VEC; ++e) a += qf[h][e] * kf[e];
         a = row_sum<LPR>(a);
+        if constexpr (kPerHead) a = a == a ? a : INFINITY;  // NaN: the maximum would pass over it (inf - inf is NaN too)
         s[u][h] = (base + u * RPL + rho < t_end) ? a : -INFINITY;
       }
     }
     float vf[U][VEC];
 #pragma unroll
     for (int u = 0; u < U; ++u) Elem<T>::widen(vr[u], vf[u]);
-    if (base + rho < t_end) {  // else the tile has no token for this row slot
+    auto top = [&](int h) {
+      float mt = m[h];
+#pragma unroll
+      for (int u = 0; u < U; ++u) mt = fmaxf(mt, s[u][h]);
+      return mt;
+    };
+    auto fold = [&](int h, float m_new) {
+      const float alpha = fast_exp2(m[h] - m_new);
+      l[h] *= alpha;
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) acc[h][e] *= alpha;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const float pu = fast_exp2(s[u][h] - m_new);
+        l[h] += pu;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) acc[h][e] += pu * vf[u][e];
+      }
+      m[h] = m_new;
+    };
+    if constexpr (kPerHead) {
 #pragma unroll
       for (int h = 0; h < G; ++h) {
-        float m_new = m[h];
-#pragma unroll
-        for (int u = 0; u < U; ++u) m_new = fmaxf(m_new, s[u][h]);
-        const float alpha = fast_exp2(m[h] - m_new);
-        l[h] *= alpha;
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) acc[h][e] *= alpha;
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const float pu = fast_exp2(s[u][h] - m_new);
-          l[h] += pu;
-#pragma unroll
-          for (int e = 0; e < VEC; ++e) acc[h][e] += pu * vf[u][e];
-        }
-        m[h] = m_new;
+        const float m_new = top(h);
+        if (m_new == kLowest) continue;
+        fold(h, m_new);
       }
+    } else if (base + rho < t_end) {
+#pragma unroll
+      for (int h = 0; h < G; ++h) fold(h, top(h));
     }
     base = next;
     if constexpr (kAhead) {
