@@ -128,7 +128,10 @@ typedef struct comem_decode_attn_plan comem_decode_attn_plan;
  * The caller allocates the workspace (device memory, 256-byte aligned) and
  * must zero-fill it once before its first use; the library keeps the
  * counters it holds at zero between calls. A workspace must not be used by
- * two calls that can run at the same time. */
+ * two calls that can run at the same time. A smaller one is taken where it
+ * still holds what a call must have (with chunk_tokens = 0, calls then use
+ * fewer, longer splits); zero-fill it again before it is given to calls with
+ * more bytes. */
 comem_status comem_decode_attn_init(const comem_decode_attn_config* cfg, int device,
                                     comem_decode_attn_plan** plan_out,
                                     size_t* workspace_bytes_out);

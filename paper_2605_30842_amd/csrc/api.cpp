@@ -39,37 +39,50 @@ constexpr int64_t kMaxChunk = 2048;                     // tokens per split, upp
 
 bool uses_mfma(const comem_decode_attn_plan& p);
 
-// After the tickets [max_batch * Hkv]: the two work-queue counters and the
-// device error word.
+// A workspace starts with the two work-queue counters and the device error
+// word, then come the tickets [max_batch * Hkv], then the partial results.
 constexpr int kCounterWords = 3;
-constexpr int kErrorWord = 2;  // index after the tickets
+constexpr int kErrorWord = 2;
 
 // Words between two tickets (log2). Atomics on one 128-byte line take their
 // turns, whichever word they name: with the tickets of 8 heads side by side,
 // the 256 workgroups of a batch-1 call waited 1.2 us for their ticket, with
-// a line each 0.4 us. So every ticket gets a line of its own where all of
-// them then still fit the counter region of the allocation-free call (a plan
-// it took with dense tickets it takes with spread ones too); a plan of more
-// sequences has its tickets closer, down to side by side: its workgroups
-// reach them at different times.
+// a line each 0.4 us. So a call spreads its tickets as far as the region at
+// the workspace's start has room for. All of that region is zero between
+// calls, however far apart the last call's tickets lay.
 constexpr int kMaxTicketShift = 5;
 
+// Words before the first ticket.
+int32_t ticket_base(int shift) { return std::max(shift > 0 ? 4 : kCounterWords, 1 << shift); }
+
 size_t ticket_region_bytes(int64_t tickets, int shift) {
-  return align256(((static_cast<size_t>(tickets) << shift) + kCounterWords) * 4);
+  return align256((static_cast<size_t>(ticket_base(shift)) + (static_cast<size_t>(tickets) << shift)) * 4);
 }
 
-int choose_ticket_shift(int64_t tickets) {
+int ticket_shift(int64_t tickets, size_t bytes) {
   int shift = kMaxTicketShift;
-  while (shift > 0 && ticket_region_bytes(tickets, shift) > comem::kScratchTicketBytes) --shift;
+  while (shift > 0 && ticket_region_bytes(tickets, shift) > bytes) --shift;
   return shift;
 }
 
-int64_t num_tickets(const comem_decode_attn_plan& p) {
-  return static_cast<int64_t>(p.cfg.max_batch) * p.cfg.num_kv_heads;
+// The region of a plan: a line for every ticket where all of them then fit
+// the counter region of the allocation-free call (a plan it took with dense
+// tickets it takes with spread ones too), closer for more sequences, whose
+// workgroups reach their tickets at different times. With a configured
+// chunk_tokens the tickets of max_batch sequences lie side by side: such a
+// call is refused when its workspace is too small, so the size stays the one
+// that the partial results need.
+size_t plan_ticket_bytes(int64_t tickets, bool planned_chunk) {
+  return ticket_region_bytes(tickets, planned_chunk ? ticket_shift(tickets, comem::kScratchTicketBytes) : 0);
 }
 
-// First of the counter words, in words from the workspace's start.
-int64_t counter_slot(const comem_decode_attn_plan& p) { return num_tickets(p) << p.ticket_shift; }
+// Where a call's tickets lie and its partial results begin.
+struct Counters {
+  size_t bytes;
+  int shift;
+  Counters(const comem_decode_attn_plan& p, int64_t batch, size_t region)
+      : bytes(region), shift(ticket_shift(batch * p.cfg.num_kv_heads, region)) {}
+};
 
 bool debug_checks(const comem_decode_attn_plan& p) { return (p.cfg.flags & COMEM_FLAG_DEBUG_CHECKS) != 0; }
 
@@ -77,20 +90,20 @@ bool debug_checks(const comem_decode_attn_plan& p) { return (p.cfg.flags & COMEM
 comem_status check_debug_workspace(const comem_decode_attn_plan& p, const void* workspace, size_t ws_bytes) {
   if (!debug_checks(p)) return COMEM_OK;
   if (workspace == nullptr) return COMEM_ERR_NULL_POINTER;
-  return ws_bytes < p.ticket_bytes ? COMEM_ERR_WORKSPACE_TOO_SMALL : COMEM_OK;
+  return ws_bytes < p.dense_bytes ? COMEM_ERR_WORKSPACE_TOO_SMALL : COMEM_OK;
 }
 
-// Workspace bytes for `slots` (sequence, split) partial results: ticket
-// counters, then per-head lse values, then per-head partial outputs.
-size_t slots_workspace_bytes(const comem_decode_attn_plan& p, int64_t slots) {
+// Workspace bytes for `slots` (sequence, split) partial results: counters and
+// tickets, then per-head lse values, then per-head partial outputs.
+size_t slots_workspace_bytes(const comem_decode_attn_plan& p, size_t counter_bytes, int64_t slots) {
   const size_t rows = static_cast<size_t>(slots) * static_cast<size_t>(p.cfg.num_q_heads);
-  return p.ticket_bytes + align256(rows * 4) + rows * static_cast<size_t>(p.cfg.head_dim) * 4;
+  return counter_bytes + align256(rows * 4) + rows * static_cast<size_t>(p.cfg.head_dim) * 4;
 }
 
 // Workspace bytes a call with `batch` sequences and `splits` splits needs.
 // A single split writes the output directly and touches no workspace.
-size_t call_workspace_bytes(const comem_decode_attn_plan& p, int64_t batch, int64_t splits) {
-  return splits <= 1 ? 0 : slots_workspace_bytes(p, batch * splits);
+size_t call_workspace_bytes(const comem_decode_attn_plan& p, const Counters& c, int64_t batch, int64_t splits) {
+  return splits <= 1 ? 0 : slots_workspace_bytes(p, c.bytes, batch * splits);
 }
 
 // Largest planned split, in tokens, of a paged call with pages of `page_size`
@@ -218,27 +231,27 @@ int64_t short_chunk(const comem_decode_attn_plan& p, int64_t batch, int64_t L) {
 // Choose tokens per split and the split count for one call. page_size is 0
 // for a contiguous cache; for a paged one the matrix-core kernel's planned
 // splits stay within kMaxSplitPages entries.
-comem_status plan_call(const comem_decode_attn_plan& p, int64_t batch, int64_t max_ctx, int64_t page_size,
-                       size_t ws_bytes, int64_t* chunk_out, int64_t* splits_out) {
+comem_status plan_call(const comem_decode_attn_plan& p, const Counters& c, int64_t batch, int64_t max_ctx,
+                       int64_t page_size, size_t ws_bytes, int64_t* chunk_out, int64_t* splits_out) {
   const int64_t L = max_ctx > 0 ? max_ctx : 1;
   const int64_t cap = page_size > 0 && uses_mfma(p) ? mfma_page_cap(page_size) : INT64_MAX;
   int64_t chunk;
   if (p.cfg.chunk_tokens > 0) {
     chunk = p.cfg.chunk_tokens;
-    if (call_workspace_bytes(p, batch, ceil_div(L, chunk)) > ws_bytes) return COMEM_ERR_WORKSPACE_TOO_SMALL;
+    if (call_workspace_bytes(p, c, batch, ceil_div(L, chunk)) > ws_bytes) return COMEM_ERR_WORKSPACE_TOO_SMALL;
   } else {
     if (uses_mfma(p)) {
       const int64_t most = std::min(long_chunk(p, batch, L), cap);
       chunk = long_call(p, batch, L) ? most : std::min(short_chunk(p, batch, L), cap);
       // A workspace too small for these splits gets those of a long call.
-      if (call_workspace_bytes(p, batch, ceil_div(L, chunk)) > ws_bytes) chunk = std::max(chunk, most);
+      if (call_workspace_bytes(p, c, batch, ceil_div(L, chunk)) > ws_bytes) chunk = std::max(chunk, most);
     } else {
       const int64_t target = kTargetWgsPerCu * p.num_cus;
       const int64_t per = ceil_div(batch * p.cfg.num_kv_heads * L, target);
       chunk = kMinChunk;
       while (chunk < per && chunk < kMaxChunk) chunk *= 2;
     }
-    while (call_workspace_bytes(p, batch, ceil_div(L, chunk)) > ws_bytes) {
+    while (call_workspace_bytes(p, c, batch, ceil_div(L, chunk)) > ws_bytes) {
       if (chunk >= L || chunk * 2 > cap) return COMEM_ERR_WORKSPACE_TOO_SMALL;
       chunk *= 2;
     }
@@ -246,6 +259,15 @@ comem_status plan_call(const comem_decode_attn_plan& p, int64_t batch, int64_t m
   *chunk_out = chunk;
   *splits_out = ceil_div(L, chunk);
   return COMEM_OK;
+}
+
+// plan_call, with dense tickets where only those leave room for the splits.
+comem_status plan_in_workspace(const comem_decode_attn_plan& p, int64_t batch, int64_t max_ctx, int64_t page_size,
+                               size_t ws_bytes, Counters* c, int64_t* chunk_out, int64_t* splits_out) {
+  const comem_status st = plan_call(p, *c, batch, max_ctx, page_size, ws_bytes, chunk_out, splits_out);
+  if (st != COMEM_ERR_WORKSPACE_TOO_SMALL) return st;
+  *c = Counters(p, batch, p.dense_bytes);
+  return plan_call(p, *c, batch, max_ctx, page_size, ws_bytes, chunk_out, splits_out);
 }
 
 comem_status validate_config(const comem_decode_attn_config& c) {
@@ -280,18 +302,19 @@ bool uses_mfma(const comem_decode_attn_plan& p) {
          (p.cfg.variant == COMEM_VARIANT_AUTO && p.cfg.dtype != COMEM_F32);
 }
 
-// The work-queue form of the matrix-core kernel keeps two counters after the
-// tickets, so it needs a workspace (of at least the ticket region).
-bool uses_queue(const comem_decode_attn_plan& p, int64_t batch, const void* workspace, size_t ws_bytes) {
+// The work-queue form of the matrix-core kernel keeps two counters beside the
+// tickets, so it needs a workspace (of at least that region).
+bool uses_queue(const comem_decode_attn_plan& p, const Counters& c, int64_t batch, const void* workspace,
+                size_t ws_bytes) {
   return uses_mfma(p) && p.cfg.variant != COMEM_VARIANT_MFMA_GRID && batch <= comem::mfma_max_queue_batch() &&
-         workspace != nullptr && ws_bytes >= p.ticket_bytes;
+         workspace != nullptr && ws_bytes >= c.bytes;
 }
 
 // The balanced form of the matrix-core kernel needs a workspace for its partial
 // results and a token count that its 24-bit arithmetic holds.
-bool uses_balanced(const comem_decode_attn_plan& p, int64_t batch, int64_t max_ctx, const void* workspace,
-                   size_t ws_bytes, size_t ticket_region) {
-  return can_balance(p, batch) && (batch == 1 || long_call(p, batch, max_ctx)) && workspace != nullptr && ws_bytes >= ticket_region + balanced_bytes(p) &&
+bool uses_balanced(const comem_decode_attn_plan& p, const Counters& c, int64_t batch, int64_t max_ctx,
+                   const void* workspace, size_t ws_bytes) {
+  return can_balance(p, batch) && (batch == 1 || long_call(p, batch, max_ctx)) && workspace != nullptr && ws_bytes >= c.bytes + balanced_bytes(p) &&
          batch * (ceil_div(max_ctx + 1, 32) + comem::kPieceTilesLight) < kMaxBalancedTiles;
 }
 
@@ -399,11 +422,11 @@ comem_status launch_append(const comem::AppendParams& a, bool paged, int32_t bat
 void fill_common(const comem_decode_attn_plan& p, comem::AttnParams& a, const void* q, const void* k,
                  const void* v, int64_t stride_token, int64_t stride_head, const int32_t* ctx_lens,
                  float* out, float* lse, void* workspace, int64_t batch, int64_t max_ctx_len, int64_t chunk,
-                 int64_t splits, bool queue, bool balanced, size_t ticket_region) {
+                 int64_t splits, bool queue, bool balanced, const Counters& c) {
   const int64_t e = elem_bytes(p.cfg);
   std::memset(&a, 0, sizeof(a));
   a.max_ctx = static_cast<int32_t>(max_ctx_len);
-  if (debug_checks(p)) a.errors = static_cast<uint32_t*>(workspace) + counter_slot(p) + kErrorWord;
+  if (debug_checks(p)) a.errors = static_cast<uint32_t*>(workspace) + kErrorWord;
   a.q = static_cast<const char*>(q);
   a.k = static_cast<const char*>(k);
   a.v = static_cast<const char*>(v);
@@ -420,16 +443,16 @@ void fill_common(const comem_decode_attn_plan& p, comem::AttnParams& a, const vo
   // An FP8 cache's K scale multiplies every score; its V scale every output.
   a.scale_log2 = p.cfg.scale * (is_fp8(p.cfg) ? p.cfg.k_scale : 1.f) * 1.4426950408889634f;
   a.out_scale = is_fp8(p.cfg) ? p.cfg.v_scale : 1.f;
-  a.queue_slot = static_cast<int32_t>(counter_slot(p));
-  a.ticket_shift = p.ticket_shift;
+  a.queue_slot = -ticket_base(c.shift);
+  a.ticket_shift = c.shift;
   if (splits > 1 || queue || balanced) {
     char* ws = static_cast<char*>(workspace);
     const size_t slots = (balanced ? 2 * static_cast<size_t>(max_ranges(p))
                                    : static_cast<size_t>(batch) * static_cast<size_t>(splits)) *
                          static_cast<size_t>(p.cfg.num_q_heads);
-    a.tickets = reinterpret_cast<uint32_t*>(ws);
-    a.lse_part = reinterpret_cast<float*>(ws + ticket_region);
-    a.o_part = reinterpret_cast<float*>(ws + ticket_region + align256(slots * 4));
+    a.tickets = reinterpret_cast<uint32_t*>(ws) + ticket_base(c.shift);
+    a.lse_part = reinterpret_cast<float*>(ws + c.bytes);
+    a.o_part = reinterpret_cast<float*>(ws + c.bytes + align256(slots * 4));
   }
 }
 
@@ -438,10 +461,9 @@ comem_status decode_contiguous(const comem_decode_attn_plan* plan, const void* q
                                const void* new_v, const void* k, const void* v, int64_t stride_token,
                                int64_t stride_head, const int64_t* seq_start, const int32_t* ctx_lens,
                                int32_t batch, int64_t max_ctx_len, float* out, float* lse, void* workspace,
-                               size_t workspace_bytes, void* hip_stream, bool fused, size_t ticket_region = 0) {
+                               size_t workspace_bytes, void* hip_stream, bool fused, bool scratch = false) {
   const comem_decode_attn_plan* p = checked(plan);
   if (p == nullptr) return COMEM_ERR_BAD_HANDLE;
-  if (ticket_region == 0) ticket_region = p->ticket_bytes;
   comem_status st = validate_common(*p, q, k, v, stride_token, stride_head, ctx_lens, batch, max_ctx_len,
                                     out, lse, workspace);
   if (st != COMEM_OK || batch == 0) return st;
@@ -452,16 +474,19 @@ comem_status decode_contiguous(const comem_decode_attn_plan* plan, const void* q
     if (!aligned(new_k, 16) || !aligned(new_v, 16)) return COMEM_ERR_MISALIGNED;
   }
   int64_t chunk = 0, splits = 0;
-  st = plan_call(*p, batch, max_ctx_len, 0, workspace == nullptr ? 0 : workspace_bytes, &chunk, &splits);
+  Counters c(*p, batch, scratch ? comem::kScratchTicketBytes : p->ticket_bytes);
+  const size_t room = workspace == nullptr ? 0 : workspace_bytes;
+  st = scratch ? plan_call(*p, c, batch, max_ctx_len, 0, room, &chunk, &splits)
+               : plan_in_workspace(*p, batch, max_ctx_len, 0, room, &c, &chunk, &splits);
   if (st != COMEM_OK) return st;
   st = check_debug_workspace(*p, workspace, workspace_bytes);
   if (st != COMEM_OK) return st;
   if (p->device == COMEM_NO_DEVICE) return COMEM_ERR_NO_DEVICE;
-  const bool balanced = uses_balanced(*p, batch, max_ctx_len, workspace, workspace_bytes, ticket_region);
-  const bool queue = uses_queue(*p, batch, workspace, workspace_bytes);
+  const bool balanced = uses_balanced(*p, c, batch, max_ctx_len, workspace, workspace_bytes);
+  const bool queue = uses_queue(*p, c, batch, workspace, workspace_bytes);
   comem::AttnParams a;
   fill_common(*p, a, q, k, v, stride_token, stride_head, ctx_lens, out, lse, workspace, batch, max_ctx_len, chunk,
-              splits, queue, balanced, ticket_region);
+              splits, queue, balanced, c);
   a.seq_start = seq_start;
   if (fused) {
     a.new_k = static_cast<const char*>(new_k);
@@ -489,7 +514,9 @@ comem_status decode_paged(const comem_decode_attn_plan* plan, const void* q, con
     if (!aligned(new_k, 16) || !aligned(new_v, 16)) return COMEM_ERR_MISALIGNED;
   }
   int64_t chunk = 0, splits = 0;
-  st = plan_call(*p, batch, max_ctx_len, page_size, workspace == nullptr ? 0 : workspace_bytes, &chunk, &splits);
+  Counters c(*p, batch, p->ticket_bytes);
+  st = plan_in_workspace(*p, batch, max_ctx_len, page_size, workspace == nullptr ? 0 : workspace_bytes, &c, &chunk,
+                         &splits);
   if (st != COMEM_OK) return st;
   // A split's block-table entries are bounded (a planned split always fits; a
   // configured chunk_tokens may not).
@@ -497,11 +524,11 @@ comem_status decode_paged(const comem_decode_attn_plan* plan, const void* q, con
   st = check_debug_workspace(*p, workspace, workspace_bytes);
   if (st != COMEM_OK) return st;
   if (p->device == COMEM_NO_DEVICE) return COMEM_ERR_NO_DEVICE;
-  const bool balanced = uses_balanced(*p, batch, max_ctx_len, workspace, workspace_bytes, p->ticket_bytes);
-  const bool queue = uses_queue(*p, batch, workspace, workspace_bytes);
+  const bool balanced = uses_balanced(*p, c, batch, max_ctx_len, workspace, workspace_bytes);
+  const bool queue = uses_queue(*p, c, batch, workspace, workspace_bytes);
   comem::AttnParams a;
   fill_common(*p, a, q, k_pages, v_pages, stride_token, stride_head, ctx_lens, out, lse, workspace, batch,
-              max_ctx_len, chunk, splits, queue, balanced, p->ticket_bytes);
+              max_ctx_len, chunk, splits, queue, balanced, c);
   a.block_table = block_table;
   a.stride_page = stride_page * elem_bytes(p->cfg);
   a.max_pages = max_pages_per_seq;
@@ -560,9 +587,9 @@ comem_status comem_decode_attn_init(const comem_decode_attn_config* cfg, int dev
   p->cfg = *cfg;
   p->device = device;
   p->num_cus = num_cus > 0 ? num_cus : kAssumedCUs;
-  // tickets (one per sequence and KV head), then the two work-queue counters
-  p->ticket_shift = choose_ticket_shift(num_tickets(*p));
-  p->ticket_bytes = ticket_region_bytes(num_tickets(*p), p->ticket_shift);
+  const int64_t tickets = static_cast<int64_t>(cfg->max_batch) * cfg->num_kv_heads;
+  p->ticket_bytes = plan_ticket_bytes(tickets, cfg->chunk_tokens == 0);
+  p->dense_bytes = ticket_region_bytes(tickets, 0);
   // Largest number of (sequence, split) slots any call within the limits plans
   // (for the matrix-core kernel: splits of 1024 tokens, or, of short calls, one
   // per compute unit);
@@ -581,7 +608,7 @@ comem_status comem_decode_attn_init(const comem_decode_attn_config* cfg, int dev
     const int64_t c = B * ceil_div(L, kMinChunk);
     if (c < slots) slots = c;
   }
-  p->workspace_bytes = slots_workspace_bytes(*p, slots);
+  p->workspace_bytes = slots_workspace_bytes(*p, p->ticket_bytes, slots);
   if (cfg->chunk_tokens == 0 && uses_mfma(*p) && cfg->variant != COMEM_VARIANT_MFMA_GRID)
     p->workspace_bytes = std::max(p->workspace_bytes, p->ticket_bytes + balanced_bytes(*p));
   // The allocation-free entry point's scratch on this device (looked up and
@@ -606,11 +633,11 @@ comem_status comem_decode_attn_device_errors(const comem_decode_attn_plan* plan,
   if (p == nullptr) return COMEM_ERR_BAD_HANDLE;
   if (workspace == nullptr || errors_out == nullptr) return COMEM_ERR_NULL_POINTER;
   if (!aligned(workspace, 256)) return COMEM_ERR_MISALIGNED;
-  if (workspace_bytes < p->ticket_bytes) return COMEM_ERR_WORKSPACE_TOO_SMALL;
+  if (workspace_bytes < p->dense_bytes) return COMEM_ERR_WORKSPACE_TOO_SMALL;
   *errors_out = 0;
   if (p->device == COMEM_NO_DEVICE) return COMEM_ERR_NO_DEVICE;
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
-  uint32_t* word = static_cast<uint32_t*>(workspace) + counter_slot(*p) + kErrorWord;
+  uint32_t* word = static_cast<uint32_t*>(workspace) + kErrorWord;
   uint32_t host = 0;
   if (hipMemcpyAsync(&host, word, sizeof(host), hipMemcpyDeviceToHost, s) != hipSuccess) return COMEM_ERR_HIP;
   if (hipStreamSynchronize(s) != hipSuccess) return COMEM_ERR_HIP;
@@ -631,7 +658,8 @@ comem_status comem_decode_attn_plan_splits(const comem_decode_attn_plan* plan, i
   if (batch < 0 || batch > p->cfg.max_batch) return COMEM_ERR_INVALID_SHAPE;
   if (max_ctx_len < 0 || max_ctx_len > p->cfg.max_ctx_len) return COMEM_ERR_INVALID_SHAPE;
   int64_t chunk = 0, splits = 0;
-  const comem_status st = plan_call(*p, batch, max_ctx_len, 0, workspace_bytes, &chunk, &splits);
+  Counters c(*p, batch, p->ticket_bytes);
+  const comem_status st = plan_in_workspace(*p, batch, max_ctx_len, 0, workspace_bytes, &c, &chunk, &splits);
   if (st != COMEM_OK) return st;
   *chunk_tokens_out = static_cast<int32_t>(chunk);
   *num_splits_out = static_cast<int32_t>(splits);
@@ -661,23 +689,23 @@ comem_status comem_decode_attn_noalloc(const comem_decode_attn_plan* plan, const
   if (!aligned(seq_start, 8)) return COMEM_ERR_MISALIGNED;
   // The splits a call with the plan's own workspace would use, and what they
   // need past the scratch's fixed counter region.
-  if (p->ticket_bytes > comem::kScratchTicketBytes) return COMEM_ERR_SCRATCH_LIMIT;
+  if (p->dense_bytes > comem::kScratchTicketBytes) return COMEM_ERR_SCRATCH_LIMIT;
   int64_t chunk = 0, splits = 0;
-  st = plan_call(*p, batch, max_ctx_len, 0, p->workspace_bytes, &chunk, &splits);
+  const Counters c(*p, batch, p->ticket_bytes);
+  st = plan_call(*p, c, batch, max_ctx_len, 0, p->workspace_bytes, &chunk, &splits);
   if (st != COMEM_OK) return st;
   // (A short call's splits never need more than those of 1024 tokens and up
   // that decide here.)
   if (uses_mfma(*p) && p->cfg.chunk_tokens == 0)
     splits = std::max(splits, ceil_div(max_ctx_len > 0 ? max_ctx_len : 1, long_chunk(*p, batch, max_ctx_len)));
-  const size_t partials = call_workspace_bytes(*p, batch, splits);
-  const size_t need = comem::kScratchTicketBytes + (partials > 0 ? partials - p->ticket_bytes : 0);
+  const size_t partials = call_workspace_bytes(*p, c, batch, splits);
+  const size_t need = comem::kScratchTicketBytes + (partials > 0 ? partials - c.bytes : 0);
   if (need > comem::kScratchBytes) return COMEM_ERR_SCRATCH_LIMIT;
   if (p->device == COMEM_NO_DEVICE) return COMEM_ERR_NO_DEVICE;
   void* scratch = comem::scratch_pointer(p->device);
   if (scratch == nullptr) return COMEM_ERR_HIP;
   return decode_contiguous(plan, q, nullptr, nullptr, k, v, stride_token, stride_head, seq_start, ctx_lens, batch,
-                           max_ctx_len, out, lse, scratch, comem::kScratchBytes, hip_stream, false,
-                           comem::kScratchTicketBytes);
+                           max_ctx_len, out, lse, scratch, comem::kScratchBytes, hip_stream, false, true);
 }
 
 comem_status comem_decode_attn_paged(const comem_decode_attn_plan* plan, const void* q,

@@ -59,8 +59,8 @@ struct AttnParams {
   float split_coef;    // balanced form: (shortest piece in 32-token tiles)^2 / tiles of the call
   int32_t whole_tiles; // balanced form of one sequence: up to so many tiles are not split
   float scale_log2;    // scale * log2(e)
-  uint32_t* tickets;   // [max_batch * Hkv] tickets 2^ticket_shift words apart, then 2 queue counters; zero between calls
-  int32_t queue_slot;  // index of the queue counters in tickets
+  uint32_t* tickets;   // [max_batch * Hkv] tickets 2^ticket_shift words apart; zero between calls
+  int32_t queue_slot;  // index of the 2 queue counters from tickets on (below 0); zero between calls
   int32_t ticket_shift;
   float* lse_part;     // [B, Hkv, S, G] (log2 units); balanced form: [Hkv, 2 * ranges, G]
   float* o_part;       // [B, Hkv, S, G, D]; balanced form: [Hkv, 2 * ranges, G, D]

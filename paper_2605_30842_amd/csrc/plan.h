@@ -28,8 +28,8 @@ struct comem_decode_attn_plan {
   comem_decode_attn_config cfg;
   int device;
   int num_cus;
-  int ticket_shift;  // log2 of the words between two tickets
-  size_t ticket_bytes;
+  size_t ticket_bytes;  // counters and tickets at the start of a workspace
+  size_t dense_bytes;   // ... with the tickets side by side
   size_t workspace_bytes;
 };
 

@@ -2,7 +2,8 @@
 
 A lane of the merging workgroup takes one batch of at most 8 splits, or
 batches of 16; 256 / (G * D / 4) lanes share an output slot (at least one).
-Tickets lie 32 words apart, closer in plans of many sequences.
+Tickets lie 32 words apart, closer in calls of many sequences (of the plan's
+most with a configured chunk).
 """
 
 import numpy as np
@@ -34,15 +35,58 @@ def test_split_counts_at_the_merge_batches(G, D, variant):
 
 
 @pytest.mark.parametrize("max_batch", [63, 64, 128, 2046, 2047, 5000])
-def test_ticket_spacing_of_large_plans(max_batch):
-    """Plans whose tickets lie 32, 16, ... 1 words apart, called with debug checks: the error word and the
-    queue counters lie past the last ticket."""
+@pytest.mark.parametrize("chunk", [32, 0])
+def test_ticket_spacing_of_large_plans(max_batch, chunk):
+    """Calls whose tickets lie 32, 16, ... 1 words apart, with debug checks: the error word and the queue counters
+    lie before the first ticket."""
     lens = [700, 0, 1, 333]
     spec = small_spec(WORKLOADS[2], lens, seed=410)
     w = generate(spec)
-    say(f"merge: tickets of a plan for {max_batch} sequences")
-    op = make_op(spec, chunk=32, max_batch=max_batch, debug_checks=True)
+    say(f"merge: tickets of a plan for {max_batch} sequences, chunk {chunk}")
+    op = make_op(spec, chunk=chunk, max_batch=max_batch, debug_checks=True)
     ro, rl = da.reference(w)
     for _ in range(2):
         check(*run(DeviceWorkload(w), op), ro, rl, "bf16", f"max_batch {max_batch}")
     assert op.device_errors() == 0
+
+
+@pytest.mark.parametrize("batch", [1, 3, 6, 12, 25, 50, 100, 200, 500])
+def test_ticket_spacing_of_the_call(batch):
+    """One plan and one workspace for 500 sequences, called with fewer and then with more: the spacing follows the
+    call, and every call finds the tickets at zero."""
+    lens = np.random.default_rng(420 + batch).integers(0, 200, size=batch).tolist()
+    lens[0] = 199
+    spec = small_spec(WORKLOADS[2], lens, seed=420).replace(num_q_heads=8, num_kv_heads=2, head_dim=64)
+    w = generate(spec)
+    say(f"merge: {batch} sequences of a plan for 500")
+    op = make_op(spec, chunk=32, max_batch=500)
+    ro, rl = da.reference(w)
+    few = generate(small_spec(WORKLOADS[2], [199], seed=421).replace(num_q_heads=8, num_kv_heads=2, head_dim=64))
+    few_ref = da.reference(few)
+    for _ in range(2):
+        check(*run(DeviceWorkload(w), op), ro, rl, "bf16", f"{batch} sequences")
+        check(*run(DeviceWorkload(few), op), *few_ref, "bf16", "one sequence")
+
+
+@pytest.mark.parametrize("ps,chunk,bound", [(0, 64, 700), (16, 64, 700), (1, 0, 4000)])
+def test_the_least_workspace(ps, chunk, bound):
+    """The smallest workspace a call takes: dense counters and its partial results."""
+    import torch
+
+    lens = [700, 0, 1, 333] if chunk else [4000]
+    spec = small_spec(WORKLOADS[4 if ps else 2], lens, max_ctx_len=bound, seed=430)
+    spec = spec.replace(layout="paged", page_size=ps) if ps else spec
+    w = generate(spec)
+    op = make_op(spec, chunk=chunk, max_batch=64)
+    splits = -(-bound // chunk) if chunk else 4  # planned: 1024 tokens
+    rows = len(lens) * splits * spec.num_q_heads
+    need = -(-(64 * spec.num_kv_heads + 3) * 4 // 256) * 256 + -(-rows * 4 // 256) * 256 + rows * spec.head_dim * 4
+    say(f"merge: a workspace of {need} bytes, page {ps}, chunk {chunk}")
+    op.workspace = torch.zeros(need, dtype=torch.uint8, device="cuda:0")
+    op.workspace_bytes = need
+    ro, rl = da.reference(w)
+    first = run(DeviceWorkload(w), op)
+    check(*first, ro, rl, "bf16", f"{need} bytes")
+    again = run(DeviceWorkload(w), op)
+    assert np.array_equal(first[0], again[0]) and np.array_equal(first[1], again[1])
+    assert not op.workspace[:-(-(64 * spec.num_kv_heads + 3) * 4 // 256) * 256].any(), "counters back at zero"

@@ -3,7 +3,7 @@
 import pytest
 
 from paper_2605_30842_amd import binding as B
-from tests.test_abi import _cfg, _noalloc_args
+from tests.test_abi import _cfg, _contig_args, _noalloc_args, _paged_args
 
 
 @pytest.mark.parametrize("max_batch", [1, 63, 64, 65, 127, 128, 1000, 2046, 2047, 2048, 4096])
@@ -47,6 +47,53 @@ def test_a_small_workspace_still_gets_every_call():
     try:
         sizes = [B.comem_decode_attn_plan_splits(p, 1, 8192, n)[0] for n in (ws, 600000, 300000, 40000, 0)]
         assert sizes == sorted(sizes) and sizes[0] == 256 and sizes[-1] >= 8192
+    finally:
+        B.comem_decode_attn_destroy(p)
+
+
+def _dense(tickets):
+    """Bytes of the counters with the tickets side by side."""
+    return -(-(tickets + 3) * 4 // 256) * 256
+
+
+def _partials(rows, d):
+    return -(-rows * 4 // 256) * 256 + rows * d * 4
+
+
+@pytest.mark.parametrize("max_batch", [1, 64, 511, 2047, 5000])
+@pytest.mark.parametrize("variant", [B.VARIANT_AUTO, B.VARIANT_VALU])
+def test_a_configured_chunk_needs_its_partial_results_and_dense_counters(max_batch, variant):
+    """The least workspace that a call with chunk_tokens takes does not depend on how far apart tickets could lie."""
+    p, ws = B.comem_decode_attn_init(_cfg(max_batch=max_batch, max_ctx_len=640, chunk_tokens=64, variant=variant),
+                                     B.NO_DEVICE)
+    try:
+        need = _dense(max_batch * 8) + _partials(max_batch * 10 * 32, 128)
+        assert ws == need
+        for n, status in ((need, B.ERR_NO_DEVICE), (need - 1, B.ERR_WORKSPACE_TOO_SMALL)):
+            args = _contig_args(p, n, batch=max_batch, max_ctx_len=640)
+            assert B.load_library().comem_decode_attn(*args.values()) == status
+    finally:
+        B.comem_decode_attn_destroy(p)
+
+
+def test_debug_checks_need_room_for_dense_counters():
+    p, ws = B.comem_decode_attn_init(_cfg(max_batch=64, max_ctx_len=64, flags=B.FLAG_DEBUG_CHECKS), B.NO_DEVICE)
+    try:
+        for n, status in ((_dense(512), B.ERR_NO_DEVICE), (_dense(512) - 1, B.ERR_WORKSPACE_TOO_SMALL)):
+            assert B.load_library().comem_decode_attn(*_contig_args(p, n, batch=1, max_ctx_len=64).values()) == status
+    finally:
+        B.comem_decode_attn_destroy(p)
+
+
+def test_one_token_pages_need_room_for_dense_counters():
+    """A split of one-token pages has at most 2016 tokens (planned: 1024), so a long paged call needs some partial
+    results."""
+    p, ws = B.comem_decode_attn_init(_cfg(max_batch=64, max_ctx_len=4000), B.NO_DEVICE)
+    try:
+        need = _dense(512) + _partials(4 * 32, 128)
+        for n, status in ((need, B.ERR_NO_DEVICE), (need - 1, B.ERR_WORKSPACE_TOO_SMALL)):
+            args = _paged_args(p, n, batch=1, max_ctx_len=4000, page_size=1, max_pages=4000)
+            assert B.load_library().comem_decode_attn_paged(*args.values()) == status
     finally:
         B.comem_decode_attn_destroy(p)
 
