@@ -442,6 +442,17 @@ def kv_cache_pair(shape, dtype, device):
     return k, v
 
 
+def _in_private_pool(t) -> bool:
+    """Whether a device tensor's memory belongs to a private pool of torch's allocator (a graph capture's)."""
+    import torch
+
+    address = t.data_ptr()
+    for segment in torch.cuda.memory_snapshot():
+        if segment["address"] <= address < segment["address"] + segment["total_size"]:
+            return tuple(segment.get("segment_pool_id", (0, 0))) != (0, 0)
+    return False
+
+
 # Shorter contexts hold fewer than two splits' worth of keys: not worth asking for a prefill workspace.
 PREFILL_SPLIT_MIN_CTX = 1024
 
@@ -691,28 +702,49 @@ class DecodeAttention:
             out = torch.empty(q.shape, dtype=torch.float32, device=q.device)
         return out, lse
 
-    def _prefill_workspace(self, batch, max_q_len, max_ctx_len, stream):
-        """Scratch of one prefill call, or None when the library would not use any. It comes from torch's allocator
-        on the call's stream and goes back to it when the call has been enqueued: no two calls share it, whatever
-        their streams and threads, and later work on the stream may reuse it."""
+    def prefill_workspace_bytes(self, batch: int, max_q_len: int, max_ctx_len: int) -> int:
+        """Bytes of a workspace that a prefill call with these bounds can use (0: none)."""
+        return comem_prefill_attn_workspace(self.plan, batch, max_q_len, max_ctx_len)
+
+    def _prefill_workspace(self, batch, max_q_len, max_ctx_len, stream, given=None):
+        """Scratch of one prefill call, or None when the library would not use any: the caller's, or else from torch's
+        allocator on the call's stream, going back to it when the call has been enqueued. So no two calls share it,
+        whatever their streams and threads, and later work on the stream may reuse it. A stream that is being captured
+        gets it only from the capture's own pool, which stays the graph's: in a capture that torch did not begin, the
+        memory would go to other tensors while the graph still points at it."""
         import torch
 
+        if given is not None:
+            _need(isinstance(given, torch.Tensor) and given.device == self._torch_device and given.is_contiguous(),
+                  f"workspace must be a contiguous tensor on {self._torch_device}")
+            return given
         if max_ctx_len < PREFILL_SPLIT_MIN_CTX:
             return None
-        nbytes = comem_prefill_attn_workspace(self.plan, batch, max_q_len, max_ctx_len)
+        nbytes = self.prefill_workspace_bytes(batch, max_q_len, max_ctx_len)
         if nbytes == 0 or not (stream is None or isinstance(stream, torch.cuda.Stream)):
             return None
+
+        def allocate():
+            ws = torch.empty(nbytes, dtype=torch.uint8, device=self._torch_device)
+            captured = ws.is_cuda and torch.cuda.is_current_stream_capturing()
+            return None if captured and not _in_private_pool(ws) else ws
+
         try:
             if stream is None:
-                return torch.empty(nbytes, dtype=torch.uint8, device=self._torch_device)
+                return allocate()
             with torch.cuda.stream(stream):
-                return torch.empty(nbytes, dtype=torch.uint8, device=self._torch_device)
+                return allocate()
         except torch.OutOfMemoryError:  # the call needs no scratch
             return None
 
     def prefill(self, q, q_start, q_lens, max_q_len: int, k, v, seq_start, ctx_lens, max_ctx_len: int, out=None,
-                lse=None, stream=None):
-        """Prefill attention of the packed new tokens q [total, Hq, D] over a contiguous cache."""
+                lse=None, stream=None, workspace=None):
+        """Prefill attention of the packed new tokens q [total, Hq, D] over a contiguous cache.
+
+        workspace: device memory of any size that no other call uses at the same time (prefill_workspace_bytes says
+        how much can be used). Without one, a call that gains from it takes scratch from torch's allocator, and in a
+        graph capture that torch did not begin does without.
+        """
         self._check_prefill(q, q_start, q_lens, max_q_len, ctx_lens, out, lse, max_ctx_len)
         self._check_cache(k, v, paged=False)
         self._check_lengths(ctx_lens, ctx_lens.shape[0], seq_start=seq_start)
@@ -720,15 +752,16 @@ class DecodeAttention:
         args = (self.plan, q.data_ptr(), q_start.data_ptr(), q_lens.data_ptr(), int(max_q_len), k.data_ptr(),
                 v.data_ptr(), k.stride(0), k.stride(1), seq_start.data_ptr(), ctx_lens.data_ptr(), ctx_lens.shape[0],
                 int(max_ctx_len), out.data_ptr(), None if lse is None else lse.data_ptr())
-        ws = self._prefill_workspace(ctx_lens.shape[0], int(max_q_len), int(max_ctx_len), stream)
+        ws = self._prefill_workspace(ctx_lens.shape[0], int(max_q_len), int(max_ctx_len), stream, workspace)
         if ws is None:
             comem_prefill_attn(*args, self._stream(stream))
         else:
-            comem_prefill_attn_split(*args, ws.data_ptr(), ws.numel(), self._stream(stream))
+            comem_prefill_attn_split(*args, ws.data_ptr(), ws.nbytes, self._stream(stream))
         return out, lse
 
     def prefill_paged(self, q, q_start, q_lens, max_q_len: int, k_pages, v_pages, block_table, ctx_lens,
-                      max_ctx_len: int, out=None, lse=None, stream=None):
+                      max_ctx_len: int, out=None, lse=None, stream=None, workspace=None):
+        """The same over a paged cache."""
         self._check_prefill(q, q_start, q_lens, max_q_len, ctx_lens, out, lse, max_ctx_len)
         self._check_cache(k_pages, v_pages, paged=True)
         self._check_lengths(ctx_lens, ctx_lens.shape[0], block_table=block_table)
@@ -737,9 +770,9 @@ class DecodeAttention:
                 v_pages.data_ptr(), k_pages.stride(0), k_pages.stride(1), k_pages.stride(2), k_pages.shape[1],
                 k_pages.shape[0], block_table.data_ptr(), block_table.shape[1], ctx_lens.data_ptr(),
                 ctx_lens.shape[0], int(max_ctx_len), out.data_ptr(), None if lse is None else lse.data_ptr())
-        ws = self._prefill_workspace(ctx_lens.shape[0], int(max_q_len), int(max_ctx_len), stream)
+        ws = self._prefill_workspace(ctx_lens.shape[0], int(max_q_len), int(max_ctx_len), stream, workspace)
         if ws is None:
             comem_prefill_attn_paged(*args, self._stream(stream))
         else:
-            comem_prefill_attn_split_paged(*args, ws.data_ptr(), ws.numel(), self._stream(stream))
+            comem_prefill_attn_split_paged(*args, ws.data_ptr(), ws.nbytes, self._stream(stream))
         return out, lse

@@ -84,3 +84,12 @@ def test_prefill_without_scratch_when_it_cannot_be_had(monkeypatch):
 
     monkeypatch.setattr(torch, "empty", full)
     assert op._prefill_workspace(1, 40, 9000, None) is None
+
+
+def test_a_given_prefill_workspace_is_checked():
+    op = _op()
+    ws = torch.empty(512, dtype=torch.uint8)
+    assert op._prefill_workspace(1, 40, 9000, None, ws) is ws
+    for bad in (ws[::2], torch.empty(512, device="meta"), 512, [0]):
+        with pytest.raises(ValueError):
+            op._prefill_workspace(1, 40, 9000, None, bad)

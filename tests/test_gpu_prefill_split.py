@@ -112,3 +112,94 @@ def test_nan_key_reaches_out_and_lse():
     out, lse = (torch.from_numpy(x) for x in run_prefill(dp, op))
     assert out[:, 4:].isnan().all() and lse[:, 4:].isnan().all()
     assert out[:, :4].isfinite().all() and lse[:, :4].isfinite().all()
+
+
+def _call(dp, op, out, lse, ps, **kw):
+    kv, s = dp.kv, dp.pw.kv.spec
+    where = kv.block_table if ps else kv.seq_start
+    (op.prefill_paged if ps else op.prefill)(dp.q, dp.q_start, dp.q_lens, dp.max_q_len, kv.k, kv.v, where, kv.ctx_lens,
+                                             s.max_ctx_len, out=out, lse=lse, **kw)
+
+
+@pytest.mark.parametrize("ps", [0, 16])
+def test_a_given_workspace(ps):
+    """A workspace of the reported size gives the bits of the wrapper's own scratch; an empty one the unsplit ones."""
+    import torch
+
+    pw = _draw([9000, 3000], [100, 1], ps, 8, 2, 128, seed=640)
+    dp, op = DevicePrefill(pw), make_op(pw.kv.spec)
+    say(f"prefill: a given workspace, page {ps}")
+    want, want_lse = (torch.from_numpy(x) for x in run_prefill(dp, op))
+    nbytes = op.prefill_workspace_bytes(2, dp.max_q_len, pw.kv.spec.max_ctx_len)
+    assert nbytes > 0
+    seen = []
+    for n in (nbytes, 2 * nbytes, nbytes // 3, 0):
+        ws = torch.full((n,), 0xFF, dtype=torch.uint8, device="cuda:0")
+        out, lse = torch.empty_like(want, device="cuda:0"), torch.empty_like(want_lse, device="cuda:0")
+        _call(dp, op, out, lse, ps, workspace=ws)
+        torch.cuda.synchronize()
+        seen.append(out.cpu())
+    assert torch.equal(seen[0], want) and torch.equal(seen[1], want)
+    assert not torch.equal(seen[3], want) and torch.allclose(seen[3], want, atol=1e-4)
+    assert torch.allclose(seen[2], want, atol=1e-4)
+
+
+def test_captured_by_torch():
+    """In a torch capture the scratch comes from the graph's pool: every replay gives the eager bits, whatever the
+    program allocates and runs between them."""
+    import torch
+
+    pw = _draw([9000, 3000], [100, 1], 16, 8, 2, 128, seed=650)
+    dp, op = DevicePrefill(pw), make_op(pw.kv.spec)
+    say("prefill: captured by torch")
+    want, want_lse = run_prefill(dp, op)
+    out = torch.empty(want.shape, device="cuda:0")
+    lse = torch.empty(want_lse.shape, device="cuda:0")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        _call(dp, op, out, lse, 16)
+        _call(dp, op, out, lse, 16)
+    for i in range(4):
+        out.zero_()
+        junk = [torch.full((1 << 22,), 1e30 * i, device="cuda:0") for _ in range(8)]
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy(), want) and np.array_equal(lse.cpu().numpy(), want_lse), f"replay {i}"
+        del junk
+
+
+def test_captured_by_another():
+    """In a capture that torch did not begin the call keeps no scratch of torch's: it runs unsplit, and replays do
+    not write to memory that other tensors have since got."""
+    import ctypes
+
+    import torch
+
+    pw = _draw([9000, 3000], [100, 1], 0, 8, 2, 128, seed=660)
+    dp, op = DevicePrefill(pw), make_op(pw.kv.spec)
+    say("prefill: captured by another")
+    want, want_lse = run_prefill(dp, op)
+    unsplit = torch.empty(want.shape, device="cuda:0")
+    lse = torch.empty(want_lse.shape, device="cuda:0")
+    _call(dp, op, unsplit, lse, 0, workspace=torch.empty(0, dtype=torch.uint8, device="cuda:0"))
+    torch.cuda.synchronize()
+    out = torch.empty(want.shape, device="cuda:0")
+    hip = ctypes.CDLL("libamdhip64.so")
+    stream = torch.cuda.Stream()
+    raw, graph, ready = ctypes.c_void_p(stream.cuda_stream), ctypes.c_void_p(), ctypes.c_void_p()
+    with torch.cuda.stream(stream):
+        assert hip.hipStreamBeginCapture(raw, 2) == 0  # relaxed
+        _call(dp, op, out, lse, 0)
+        assert hip.hipStreamEndCapture(raw, ctypes.byref(graph)) == 0
+    assert hip.hipGraphInstantiate(ctypes.byref(ready), graph, None, None, 0) == 0
+    with torch.cuda.stream(stream):
+        held = [torch.full((1 << 20,), 7.0, device="cuda:0") for _ in range(64)]
+    for i in range(3):
+        stream.synchronize()
+        out.zero_()
+        torch.cuda.synchronize()
+        assert hip.hipGraphLaunch(ready, raw) == 0
+        stream.synchronize()
+        assert torch.equal(out, unsplit), f"replay {i}"
+        assert all(bool((h == 7.0).all()) for h in held), f"replay {i}: another tensor's memory"
+    assert hip.hipGraphExecDestroy(ready) == 0 and hip.hipGraphDestroy(graph) == 0
