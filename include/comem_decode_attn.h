@@ -150,11 +150,13 @@ const char* comem_status_string(comem_status status);
  * splits, except that a matrix-core call with chunk_tokens = 0 and a
  * workspace of the size comem_decode_attn_init reports shares the 32-token
  * tiles out differently: of one sequence, split j of n takes the tiles j,
- * j + n, ...; of several with a long bound (batch * max_ctx_len of a thousand
- * tokens and more for every compute unit and sequence), the tiles of all
- * sequences are cut into equal ranges, so that a sequence's splits follow
- * from the lengths of all sequences in the call. Nothing depends on timing:
- * the same call always returns the same bits. */
+ * j + n, ...; of several with a long bound (from about a thousand tokens a
+ * sequence), the tiles of all sequences are cut into equal ranges, so that a
+ * sequence's splits, and with them the rounding of its results, follow from
+ * the lengths of all sequences in the call. With a configured chunk_tokens, COMEM_VARIANT_MFMA_GRID or
+ * COMEM_VARIANT_VALU they follow from its own length and the call's batch and
+ * max_ctx_len alone. Nothing depends on timing: the same call always returns
+ * the same bits. */
 comem_status comem_decode_attn_plan_splits(const comem_decode_attn_plan* plan, int32_t batch,
                                            int64_t max_ctx_len, size_t workspace_bytes,
                                            int32_t* chunk_tokens_out, int32_t* num_splits_out);

@@ -129,3 +129,18 @@ def test_one_sequence_in_strided_tiles(base, ps, length):
     torch.cuda.synchronize()
     same = lambda x, y: torch.equal(x.view(torch.uint8), y.view(torch.uint8))  # noqa: E731 (NaN poison compares as bytes)
     assert same(a.k, b.k) and same(a.v, b.v) and torch.equal(out_a, out_b)
+
+
+@pytest.mark.parametrize("chunk,variant", [(256, "auto"), (0, "mfma_grid"), (0, "valu")])
+def test_forms_without_ranges_do_not_see_the_neighbours(chunk, variant):
+    """A sequence's bits stay the same whatever the other sequences' lengths are."""
+    import dataclasses
+
+    lens = _ragged(9, 5000, 31)
+    w = generate(_spec(2, lens, 16384))
+    op = make_op(w.spec, chunk=chunk, variant=variant)
+    say(f"neighbours: chunk {chunk}, {variant}")
+    out, lse = run(DeviceWorkload(w), op)
+    other = np.array([n if b % 2 else max(1, n // 3) for b, n in enumerate(lens)])
+    out2, lse2 = run(DeviceWorkload(dataclasses.replace(w, ctx_lens=other)), op)
+    assert np.array_equal(out[1::2], out2[1::2]) and np.array_equal(lse[1::2], lse2[1::2])
