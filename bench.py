@@ -121,7 +121,7 @@ def _counter_medians(path):
     for f in glob.glob(os.path.join(path, "**", "*counter_collection.csv"), recursive=True):
         for r in csv.DictReader(open(f)):
             k = r["Kernel_Name"]
-            kind = "attn" if ("decode_" in k or "prefill_" in k) else ("copy" if "copy_kernel" in k else None)
+            kind = "attn" if ("decode_" in k or "prefill_mfma" in k) else ("copy" if "copy_kernel" in k else None)
             if kind:
                 vals.setdefault((kind, r["Counter_Name"]), []).append(float(r["Counter_Value"]))
     return {k: sorted(v)[len(v) // 2] for k, v in vals.items()}
@@ -185,8 +185,8 @@ def _derived_counters(d, tag, kv_bytes):
 def _short_kernel_name(full):
     """decode_mfma_queue_kernel<128, Layout 1, true> -> decode_mfma_queue_D128_paged_fp8 (and similar).
 
-    A bool template argument is the FP8 switch of the MFMA decode kernels
-    and the paged switch of the others.
+    A bool template argument is the FP8 switch of the MFMA decode kernels,
+    the split switch of the prefill kernel and the paged switch of the others.
     """
     import re
 
@@ -208,6 +208,8 @@ def _short_kernel_name(full):
             name += "_f32"
         elif a in ("true", "false") and base.startswith("decode_mfma"):
             name += "_fp8" if a == "true" else ""
+        elif a in ("true", "false") and base.startswith("prefill"):
+            name += "_split" if a == "true" else ""
         elif a in ("true", "false"):
             name += "_paged" if a == "true" else "_contig"
     return name
@@ -244,7 +246,7 @@ def summarize(a):
         stats = _kernel_stats(os.path.join(d, "prof", f"{tag}{i}"))
         if not stats:
             continue
-        key = {"w": "decode_", "p": "prefill_", "a": "kv_append"}[tag]
+        key = {"w": "decode_", "p": "prefill_mfma", "a": "kv_append"}[tag]
         attn = [r for r in stats if key in r["Name"]]
         if tag == "a":
             # K and V rows of every (sequence, KV head): read from the inputs, written to the cache
@@ -563,7 +565,10 @@ def _measure_decode(a, wl, placement, steps, warmup, op_kind="attention", single
     scales = dict(k_scale=spec.k_scale, v_scale=spec.v_scale) if spec.dtype == "fp8" else {}
     op = DecodeAttention(spec.num_q_heads, spec.num_kv_heads, spec.head_dim, spec.dtype, float(spec.scale),
                          spec.batch, spec.max_ctx_len, chunk_tokens=a.chunk, variant=a.variant, **scales)
-    chunk, splits = op.splits(spec.batch, spec.max_ctx_len)
+    # Split sizes that the host alone fixes. A planned matrix-core call may take its splits from the lengths
+    # on the device instead, and the plan's own sizes then say nothing about what ran.
+    fixed = a.chunk > 0 or a.variant in ("valu", "mfma_grid") or spec.dtype == "f32"
+    chunk, splits = op.splits(spec.batch, spec.max_ctx_len) if fixed else (None, None)
     out = torch.zeros((spec.batch, spec.num_q_heads, spec.head_dim), dtype=torch.float32, device=dev)
     lse = torch.empty((spec.batch, spec.num_q_heads), dtype=torch.float32, device=dev)
     new_k, new_v = (dev_t(x) for x in draw_new_rows(spec, seed=spec.seed + 100))
@@ -694,9 +699,9 @@ def _read_ceiling(nbytes, steps, blocks=4096):
             "buffers_cycled": copies}
 
 
-def _read_kv_heads(spec, tokens, chunk, placement, steps):
-    """A bare read of the headline cache with the decode kernel's grid and per-lane loads
-    (comem_probe_read_kv_heads), timed like the decode steps (graph replays, cycling over KV copies placed
+def _read_kv_heads(spec, tokens, placement, steps):
+    """A bare read of the headline cache with the decode kernel's grid (one workgroup per compute unit and KV
+    head's share), tile order and per-lane loads (comem_probe_read_kv_heads), timed like the decode steps (graph replays, cycling over KV copies placed
     as in the decode measurement): the ceiling of the kernel's access pattern. None where it does not apply
     (paged or ragged caches, head_dim other than 128, fp32, or lengths not a multiple of the split)."""
     import torch
@@ -704,8 +709,10 @@ def _read_kv_heads(spec, tokens, chunk, placement, steps):
     from paper_2605_30842_amd import binding
 
     head_bytes = {"bf16": 256, "fp8": 128}.get(spec.dtype)
+    splits = max(1, torch.cuda.get_device_properties(0).multi_processor_count // spec.num_kv_heads)
+    chunk = tokens // splits
     if (spec.layout != "contiguous" or spec.batch != 1 or spec.head_dim != 128 or head_bytes is None or
-            tokens % chunk != 0 or chunk % 128 != 0):
+            chunk == 0 or tokens % splits != 0 or chunk % 128 != 0):
         return None
     binding.load_probe_library()
     dev = torch.device("cuda:0")
@@ -747,7 +754,7 @@ def _read_kv_heads(spec, tokens, chunk, placement, steps):
     us = e0.elapsed_time(e1) * 1e3 / (reps * per_graph)
     del kv, sink, g
     torch.cuda.empty_cache()
-    return {"bytes": kv_bytes, "split_tokens": chunk, "kv_placement": placement, "us_per_call": round(us, 3),
+    return {"bytes": kv_bytes, "splits": splits, "kv_placement": placement, "us_per_call": round(us, 3),
             "GBps": round(kv_bytes / (us * 1e-6) / 1e9, 1),
             "frac_of_peak": round(kv_bytes / (us * 1e-6) / 1e9 / PEAK_HBM_GBPS, 4), "buffers_cycled": copies}
 
@@ -825,7 +832,7 @@ def main():
             also[rw["spec"].name] = dict(_summary(rw), kv_placement=a.kv_placement)
             print(f"# {rw['spec'].name}: {rw['ms'] * 1e3:.3f} us/step", file=sys.stderr, flush=True)
         ceiling = {"read_4GiB": _read_ceiling(4 << 30, 160), "read_same_bytes": _read_ceiling(kv_bytes, a.steps)}
-        pattern = _read_kv_heads(spec, int(r["ctx_len_total"]), r["chunk"], a.kv_placement, a.steps)
+        pattern = _read_kv_heads(spec, int(r["ctx_len_total"]), a.kv_placement, a.steps)
         if pattern is not None:
             ceiling["read_kernel_pattern"] = pattern
         print(f"# read ceiling: {ceiling}", file=sys.stderr, flush=True)

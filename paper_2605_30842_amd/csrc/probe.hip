@@ -93,21 +93,21 @@ __global__ __launch_bounds__(256) void read_kv_heads_kernel(const char* k, const
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, c = lane & 15, g = lane >> 4;
   const char* kh = k + static_cast<int64_t>(h) * HB;
   const char* vh = v + static_cast<int64_t>(h) * HB;
-  const int64_t t0 = static_cast<int64_t>(j) * chunk;
-  const int ntiles = chunk / 32;
+  const int64_t t0 = 32 * static_cast<int64_t>(j), step = 32 * static_cast<int64_t>(gridDim.x);
+  const int ntiles = chunk / 32;  // tiles j, j + n, ... of n splits: the last is below n * ntiles = tokens / 32
   uint32_t acc = 0;
   KvTile<HB> A, B;
   int t = w;
-  load_kv_tile<HB>(A, kh, vh, t0 + 32 * t, stride, c, g);
+  load_kv_tile<HB>(A, kh, vh, t0 + step * t, stride, c, g);
   for (;;) {
     int nx = t + 4;
-    load_kv_tile<HB>(B, kh, vh, t0 + 32 * (nx < ntiles ? nx : t), stride, c, g);
+    load_kv_tile<HB>(B, kh, vh, t0 + step * (nx < ntiles ? nx : t), stride, c, g);
     __builtin_amdgcn_sched_barrier(0);
     acc ^= fold_kv_tile<HB>(A);
     if (nx >= ntiles) break;
     t = nx;
     nx = t + 4;
-    load_kv_tile<HB>(A, kh, vh, t0 + 32 * (nx < ntiles ? nx : t), stride, c, g);
+    load_kv_tile<HB>(A, kh, vh, t0 + step * (nx < ntiles ? nx : t), stride, c, g);
     __builtin_amdgcn_sched_barrier(0);
     acc ^= fold_kv_tile<HB>(B);
     if (nx >= ntiles) break;
