@@ -599,9 +599,11 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(const AttnPara
     // of the cache, where runs of a power of two of tokens start whole MiB
     // apart (us per call, runs / strided, contiguous: 32768 tokens FP8 16.9 /
     // 15.9 eager, 18.6 / 17.5 with cold caches, bf16 25.1 / 25.0 and 27.8 /
-    // 27.2; 6001, 20000 and 100001 within 0.7%). Pages lie scattered anyway
-    // and run 0-0.9% slower; they keep the same splits, so that a paged call
-    // returns the contiguous call's bits.
+    // 27.2; eager, 8192 12.8 / 12.6, 16384 16.8 / 16.6, 65536 48.7 / 46.5 and
+    // FP8 28.5 / 26.4, 131072 86.3 / 83.7 and 49.0 / 48.7; 6001, 20000 and
+    // 100001 within 0.7%). Pages lie scattered anyway (16 tokens: 16384 16.9 /
+    // 16.8, 32768 26.0 / 25.8; 64: 25.7 / 25.9); they keep the same splits, so
+    // that a paged call returns the contiguous call's bits.
     const int n = parts.count;
     t0 = 32 * j;
     stride = 32 * n;
