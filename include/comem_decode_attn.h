@@ -131,7 +131,7 @@ typedef struct comem_decode_attn_plan comem_decode_attn_plan;
  * two calls that can run at the same time. A smaller one is taken where it
  * still holds what a call must have (with chunk_tokens = 0, calls then use
  * fewer, longer splits); zero-fill it again before it is given to calls with
- * more bytes. */
+ * more bytes, or of a plan with other limits, heads or chunk_tokens. */
 comem_status comem_decode_attn_init(const comem_decode_attn_config* cfg, int device,
                                     comem_decode_attn_plan** plan_out,
                                     size_t* workspace_bytes_out);
@@ -153,10 +153,10 @@ const char* comem_status_string(comem_status status);
  * j + n, ...; of several with a long bound (from about a thousand tokens a
  * sequence), the tiles of all sequences are cut into equal ranges, so that a
  * sequence's splits, and with them the rounding of its results, follow from
- * the lengths of all sequences in the call. With a configured chunk_tokens, COMEM_VARIANT_MFMA_GRID or
- * COMEM_VARIANT_VALU they follow from its own length and the call's batch and
- * max_ctx_len alone. Nothing depends on timing: the same call always returns
- * the same bits. */
+ * the lengths of all sequences in the call. With a configured chunk_tokens,
+ * COMEM_VARIANT_MFMA_GRID or COMEM_VARIANT_VALU they follow from its own length
+ * and the call's batch and max_ctx_len alone. Nothing depends on timing: the
+ * same call always returns the same bits. */
 comem_status comem_decode_attn_plan_splits(const comem_decode_attn_plan* plan, int32_t batch,
                                            int64_t max_ctx_len, size_t workspace_bytes,
                                            int32_t* chunk_tokens_out, int32_t* num_splits_out);

@@ -76,6 +76,16 @@ size_t plan_ticket_bytes(int64_t tickets, bool planned_chunk) {
   return ticket_region_bytes(tickets, planned_chunk ? ticket_shift(tickets, comem::kScratchTicketBytes) : 0);
 }
 
+// Bytes of that region in a workspace of ws_bytes. A smaller one than the plan
+// reports gives up the room between tickets first, so that it holds the
+// partial results of every call that dense tickets leave room for. The size
+// must not depend on the call: a region that one call counts in would hold
+// another's partial results.
+size_t counter_region(const comem_decode_attn_plan& p, size_t ws_bytes) {
+  const size_t least = p.dense_bytes + p.partial_bytes;
+  return ws_bytes < least ? p.dense_bytes : std::min(p.ticket_bytes, p.dense_bytes + (ws_bytes - least) / 256 * 256);
+}
+
 // Where a call's tickets lie and its partial results begin.
 struct Counters {
   size_t bytes;
@@ -261,15 +271,6 @@ comem_status plan_call(const comem_decode_attn_plan& p, const Counters& c, int64
   return COMEM_OK;
 }
 
-// plan_call, with dense tickets where only those leave room for the splits.
-comem_status plan_in_workspace(const comem_decode_attn_plan& p, int64_t batch, int64_t max_ctx, int64_t page_size,
-                               size_t ws_bytes, Counters* c, int64_t* chunk_out, int64_t* splits_out) {
-  const comem_status st = plan_call(p, *c, batch, max_ctx, page_size, ws_bytes, chunk_out, splits_out);
-  if (st != COMEM_ERR_WORKSPACE_TOO_SMALL) return st;
-  *c = Counters(p, batch, p.dense_bytes);
-  return plan_call(p, *c, batch, max_ctx, page_size, ws_bytes, chunk_out, splits_out);
-}
-
 comem_status validate_config(const comem_decode_attn_config& c) {
   if (c.num_q_heads <= 0 || c.num_kv_heads <= 0 || c.num_q_heads % c.num_kv_heads != 0)
     return COMEM_ERR_INVALID_SHAPE;
@@ -314,7 +315,8 @@ bool uses_queue(const comem_decode_attn_plan& p, const Counters& c, int64_t batc
 // results and a token count that its 24-bit arithmetic holds.
 bool uses_balanced(const comem_decode_attn_plan& p, const Counters& c, int64_t batch, int64_t max_ctx,
                    const void* workspace, size_t ws_bytes) {
-  return can_balance(p, batch) && (batch == 1 || long_call(p, batch, max_ctx)) && workspace != nullptr && ws_bytes >= c.bytes + balanced_bytes(p) &&
+  return can_balance(p, batch) && (batch == 1 || long_call(p, batch, max_ctx)) && workspace != nullptr &&
+         ws_bytes >= c.bytes + balanced_bytes(p) &&
          batch * (ceil_div(max_ctx + 1, 32) + comem::kPieceTilesLight) < kMaxBalancedTiles;
 }
 
@@ -474,10 +476,9 @@ comem_status decode_contiguous(const comem_decode_attn_plan* plan, const void* q
     if (!aligned(new_k, 16) || !aligned(new_v, 16)) return COMEM_ERR_MISALIGNED;
   }
   int64_t chunk = 0, splits = 0;
-  Counters c(*p, batch, scratch ? comem::kScratchTicketBytes : p->ticket_bytes);
   const size_t room = workspace == nullptr ? 0 : workspace_bytes;
-  st = scratch ? plan_call(*p, c, batch, max_ctx_len, 0, room, &chunk, &splits)
-               : plan_in_workspace(*p, batch, max_ctx_len, 0, room, &c, &chunk, &splits);
+  const Counters c(*p, batch, scratch ? comem::kScratchTicketBytes : counter_region(*p, room));
+  st = plan_call(*p, c, batch, max_ctx_len, 0, room, &chunk, &splits);
   if (st != COMEM_OK) return st;
   st = check_debug_workspace(*p, workspace, workspace_bytes);
   if (st != COMEM_OK) return st;
@@ -514,9 +515,9 @@ comem_status decode_paged(const comem_decode_attn_plan* plan, const void* q, con
     if (!aligned(new_k, 16) || !aligned(new_v, 16)) return COMEM_ERR_MISALIGNED;
   }
   int64_t chunk = 0, splits = 0;
-  Counters c(*p, batch, p->ticket_bytes);
-  st = plan_in_workspace(*p, batch, max_ctx_len, page_size, workspace == nullptr ? 0 : workspace_bytes, &c, &chunk,
-                         &splits);
+  const size_t room = workspace == nullptr ? 0 : workspace_bytes;
+  const Counters c(*p, batch, counter_region(*p, room));
+  st = plan_call(*p, c, batch, max_ctx_len, page_size, room, &chunk, &splits);
   if (st != COMEM_OK) return st;
   // A split's block-table entries are bounded (a planned split always fits; a
   // configured chunk_tokens may not).
@@ -608,7 +609,8 @@ comem_status comem_decode_attn_init(const comem_decode_attn_config* cfg, int dev
     const int64_t c = B * ceil_div(L, kMinChunk);
     if (c < slots) slots = c;
   }
-  p->workspace_bytes = slots_workspace_bytes(*p, p->ticket_bytes, slots);
+  p->partial_bytes = slots_workspace_bytes(*p, 0, slots);
+  p->workspace_bytes = p->ticket_bytes + p->partial_bytes;
   if (cfg->chunk_tokens == 0 && uses_mfma(*p) && cfg->variant != COMEM_VARIANT_MFMA_GRID)
     p->workspace_bytes = std::max(p->workspace_bytes, p->ticket_bytes + balanced_bytes(*p));
   // The allocation-free entry point's scratch on this device (looked up and
@@ -658,8 +660,8 @@ comem_status comem_decode_attn_plan_splits(const comem_decode_attn_plan* plan, i
   if (batch < 0 || batch > p->cfg.max_batch) return COMEM_ERR_INVALID_SHAPE;
   if (max_ctx_len < 0 || max_ctx_len > p->cfg.max_ctx_len) return COMEM_ERR_INVALID_SHAPE;
   int64_t chunk = 0, splits = 0;
-  Counters c(*p, batch, p->ticket_bytes);
-  const comem_status st = plan_in_workspace(*p, batch, max_ctx_len, 0, workspace_bytes, &c, &chunk, &splits);
+  const Counters c(*p, batch, counter_region(*p, workspace_bytes));
+  const comem_status st = plan_call(*p, c, batch, max_ctx_len, 0, workspace_bytes, &chunk, &splits);
   if (st != COMEM_OK) return st;
   *chunk_tokens_out = static_cast<int32_t>(chunk);
   *num_splits_out = static_cast<int32_t>(splits);

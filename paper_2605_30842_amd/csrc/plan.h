@@ -30,6 +30,7 @@ struct comem_decode_attn_plan {
   int num_cus;
   size_t ticket_bytes;  // counters and tickets at the start of a workspace
   size_t dense_bytes;   // ... with the tickets side by side
+  size_t partial_bytes; // partial results of the most splits that any call needs
   size_t workspace_bytes;
 };
 

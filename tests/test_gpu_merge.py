@@ -68,6 +68,28 @@ def test_ticket_spacing_of_the_call(batch):
         check(*run(DeviceWorkload(few), op), *few_ref, "bf16", "one sequence")
 
 
+def test_calls_of_a_small_workspace_agree_on_the_counters():
+    """A long call over one-token pages whose partial results leave no room between tickets, then a call of eight
+    short sequences that spread tickets would leave room for: it finds them at zero, not at the first one's
+    results."""
+    import torch
+
+    spec = small_spec(WORKLOADS[4], [64000], max_ctx_len=64000, seed=440).replace(layout="paged", page_size=1)
+    few = small_spec(WORKLOADS[2], [700, 650, 1, 700, 0, 699, 300, 700], max_ctx_len=700, seed=441)
+    op = make_op(spec, max_batch=64)
+    rows = 63 * spec.num_q_heads  # splits of 1024 tokens
+    need = -(-(64 * spec.num_kv_heads + 3) * 4 // 256) * 256 + -(-rows * 4 // 256) * 256 + rows * spec.head_dim * 4
+    op.workspace = torch.zeros(need, dtype=torch.uint8, device="cuda:0")
+    op.workspace_bytes = need
+    wl, ws = generate(spec), generate(few)
+    rl, rs = da.reference(wl), da.reference(ws)
+    say(f"merge: two calls in a workspace of {need} bytes")
+    dl, ds = DeviceWorkload(wl), DeviceWorkload(ws)
+    for _ in range(2):
+        check(*run(dl, op), *rl, "bf16", "long")
+        check(*run(ds, op), *rs, "bf16", "short")
+
+
 @pytest.mark.parametrize("ps,chunk,bound", [(0, 64, 700), (16, 64, 700), (1, 0, 4000)])
 def test_the_least_workspace(ps, chunk, bound):
     """The smallest workspace a call takes: dense counters and its partial results."""
