@@ -262,7 +262,11 @@ comem_status plan_call(const comem_decode_attn_plan& p, const Counters& c, int64
       while (chunk < per && chunk < kMaxChunk) chunk *= 2;
     }
     while (call_workspace_bytes(p, c, batch, ceil_div(L, chunk)) > ws_bytes) {
-      if (chunk >= L || chunk * 2 > cap) return COMEM_ERR_WORKSPACE_TOO_SMALL;
+      if (chunk >= L || chunk * 2 > cap) {
+        if (L > cap) return COMEM_ERR_WORKSPACE_TOO_SMALL;
+        chunk = cap;  // a whole sequence needs no partial results
+        break;
+      }
       chunk *= 2;
     }
   }

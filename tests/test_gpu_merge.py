@@ -68,6 +68,18 @@ def test_ticket_spacing_of_the_call(batch):
         check(*run(DeviceWorkload(few), op), *few_ref, "bf16", "one sequence")
 
 
+@pytest.mark.parametrize("ps,bound", [(1, 2016), (2, 4064)])
+def test_whole_sequences_of_small_pages_without_a_workspace(ps, bound):
+    """The longest sequence that runs whole in pages of 1 and 2 tokens, in a call that has no workspace."""
+    spec = small_spec(WORKLOADS[4], [bound, 0, 31, bound - 1], max_ctx_len=bound, seed=450)
+    spec = spec.replace(layout="paged", page_size=ps)
+    w = generate(spec)
+    op = make_op(spec, max_batch=64)
+    op.workspace_bytes = 0
+    say(f"merge: no workspace, page {ps}, {bound} tokens")
+    check(*run(DeviceWorkload(w), op), *da.reference(w), "bf16", f"page {ps}")
+
+
 def test_calls_of_a_small_workspace_agree_on_the_counters():
     """A long call over one-token pages whose partial results leave no room between tickets, then a call of eight
     short sequences that spread tickets would leave room for: it finds them at zero, not at the first one's

@@ -85,6 +85,19 @@ def test_debug_checks_need_room_for_dense_counters():
         B.comem_decode_attn_destroy(p)
 
 
+@pytest.mark.parametrize("page,L", [(1, 2016), (2, 4064)])
+def test_a_call_that_pages_allow_whole_needs_no_workspace(page, L):
+    """A planned split spans at most 2046 pages; up to that length a sequence can run whole, whatever the plan
+    prefers. One token more needs partial results."""
+    p, ws = B.comem_decode_attn_init(_cfg(max_batch=64, max_ctx_len=8192), B.NO_DEVICE)
+    try:
+        for n, status in ((L, B.ERR_NO_DEVICE), (L + 1, B.ERR_WORKSPACE_TOO_SMALL)):
+            args = _paged_args(p, 0, batch=48, max_ctx_len=n, page_size=page, max_pages=n, workspace=None)
+            assert B.load_library().comem_decode_attn_paged(*args.values()) == status
+    finally:
+        B.comem_decode_attn_destroy(p)
+
+
 def test_one_token_pages_need_room_for_dense_counters():
     """A split of one-token pages has at most 2016 tokens (planned: 1024), so a long paged call needs some partial
     results."""
