@@ -744,7 +744,7 @@ __global__ __launch_bounds__(kPrefillMergeThreads) void prefill_merge_kernel(con
     if (i >= M) continue;
     const float* lp = p.lse_part + part0 + row;
     const float* op = p.o_part + (part0 + row) * D + d0;
-    float m = -INFINITY, wsum = 0.f;
+    float m = kLowest, wsum = 0.f;  // finite: a batch of splits may hold no key with a weight
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int s0 = 0; s0 < p.splits; s0 += kBatch) {
       float l2[kBatch];
@@ -761,7 +761,7 @@ __global__ __launch_bounds__(kPrefillMergeThreads) void prefill_merge_kernel(con
         if (s0 + k >= p.splits) l2[k] = -INFINITY;
         mn = fmaxf(mn, l2[k]);
       }
-      const float a = m == -INFINITY ? 0.f : fast_exp2(m - mn);  // the first split holds key 0: mn is finite
+      const float a = fast_exp2(m - mn);
       acc = make_float4(acc.x * a, acc.y * a, acc.z * a, acc.w * a);
       wsum *= a;
 #pragma unroll

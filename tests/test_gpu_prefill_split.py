@@ -116,6 +116,21 @@ def test_nan_key_reaches_out_and_lse():
     assert out[:, :4].isfinite().all() and lse[:, :4].isfinite().all()
 
 
+@pytest.mark.parametrize("keys", [1, 3000, 8000])
+def test_keys_of_score_minus_infinity_in_the_first_splits(keys):
+    """Rows whose first keys have scores of -inf, as many as several splits hold: those splits have weight 0."""
+    pw = _draw([9000], [5], 0, 2, 2, 128, seed=640)
+    t0 = int(pw.kv.seq_start[0])
+    pw.q[:, 1, 7] = 0x3F80  # 1
+    pw.kv.k[t0:t0 + keys, 1, 7] = 0xFF80  # -inf
+    dp, op = DevicePrefill(pw), make_op(pw.kv.spec)
+    splits = next(n for n in range(1, 65) if _bytes(2, n, 128) == op.prefill_workspace_bytes(1, 5, 9000))
+    say(f"prefill split: {keys} keys of score -inf, {splits} splits")
+    assert splits > 8, "the first batch of the merge holds 8"
+    want = pa.reference(pw)
+    check_prefill(*run_prefill(dp, op), *want, pa.reference(abs_values(pw))[0], f"{keys} keys")
+
+
 def _call(dp, op, out, lse, ps, **kw):
     kv, s = dp.kv, dp.pw.kv.spec
     where = kv.block_table if ps else kv.seq_start
